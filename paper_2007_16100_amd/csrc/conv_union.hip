@@ -18,185 +18,228 @@ __device__ __forceinline__ void static_for(F&& f) {
 // ---------------------------------------------------------------------------
 // neighbour-table kernel (3x3x3 maps)
 // ---------------------------------------------------------------------------
-// One workgroup of NW waves per CU; wave w owns RB blocks of 16 output rows and
-// all output channels (NB blocks of 16).  The accumulators of a block are
-// D = W^T G^T fragments: lane (r16, g) holds output channels nb*16 + 4g .. 4g+3
-// of row r16, which is also the order in which they are stored.
+// A workgroup of NW waves computes R = 16 RB NW output rows times NBT blocks of 16 output channels
+// (NB / NBT workgroups share the rows).  A wave owns RB blocks of 16 rows; the accumulators of a
+// block are D = W^T G^T fragments: lane (r16, g) holds output channels nb*16 + 4g .. 4g+3 of row
+// r16, which is also the order in which they are stored.
 //
-// The 27 offsets run in phases of PH: at the start of a phase the workgroup
-// copies W of the phase's offsets into LDS with global->LDS loads (one barrier
-// before, one wait for every load of the wave and one barrier after);
-// inside a phase the waves never synchronize and load no weights, each one
-// streaming its own rows:
-//   step k: loads the neighbour indices of offset k+3 and gathers the rows of
-//           offset k+1 (a block with no neighbour at that offset, or a lane
-//           whose row has none, reads zeros from outside the buffer), then
-//           multiplies the rows gathered for offset k by W[k] one 32-channel
-//           slab at a time, skipping blocks without a neighbour at k.
-// All other loads are ordinary vector-memory loads the compiler sees, the same
-// number every step, so its waits (which count outstanding loads in issue
-// order) stay exact and a step waits for its own rows only: the weight copies
-// it does not see are all complete (vmcnt 0) before the phase starts.
+// What bounds it: at one 88k-voxel sweep 96 -> 96 the parts of a workgroup's life (weight copies, row
+// gathers, fragment reads, products) take 3 / 9 / 11 / 9 of its 48 us and mostly add up, and below
+// ~50k rows a workgroup's own chain of 27 offsets is the kernel's time, however few workgroups there
+// are.  So:
+// * the workgroup's rows of the neighbour table go to LDS first, in one coalesced copy: read offset by
+//   offset from memory each 4-byte index cost a lane its own cache line, as much as a gathered row;
+// * the weights of a group of PH offsets are copied global->LDS while the group before is multiplied
+//   (two buffers, one barrier per group, instead of a stop for the copy at each group);
+// * the tile is chosen per call (union_class below): 384 or 512 rows where the rows fill the chip,
+//   down to 64 rows and a slice of the output channels where they do not.  256 -> 256 on 3,161 rows:
+//   107 -> 31 us, 128 -> 128 on 7,697: 37 -> 17 us, 96 -> 96 on 52,357: 46 -> 33 us, on 88,119: 52 ->
+//   49 us, on 356,951: 171 -> 160 us.
+//
+// A step is one offset's (k) slab of KS 32-channel chunks; the rows of RA steps are in flight while
+// one is multiplied (a lane whose row has no neighbour reads from outside the buffer, which costs
+// nothing and returns zeros, so every step issues the same loads and the compiler's waits stay exact);
+// blocks with no neighbour at k skip their products.  The copies the compiler does not see are
+// issued after the group's first rows have arrived and waited for by count before the barrier: the
+// loads issued after them are the rows of the steps ahead.
 constexpr int kUK3 = 27;
-constexpr int kNAhead = 3;  // neighbour indices: steps ahead
-constexpr int kRAhead = 1;  // gathered rows: steps ahead
 
-template <int DT, int KCH, int NB, int RB, int NW, int PH>
-__global__ __launch_bounds__(64 * NW) void k_conv_union(
+// shape of a workgroup's tile; valid when it fits in LDS and in the registers of a wave
+template <int KCH, int NB, int CLS>
+struct UnionTile {
+    // output-channel blocks of a workgroup: all of them (at most 8) in the classes for many rows, at
+    // most half of them in the classes that spread few rows over the chip
+    static constexpr int NBL = NB > 8 ? 8 : NB;
+    static constexpr int NBS = NB == 2 ? 2 : NB == 4 ? 2 : NB == 6 ? (KCH == 8 ? 3 : 2) : 4;
+    static constexpr int NBT = CLS < 3 ? NBL : NBS;
+    static constexpr int FR = KCH * NBT;  // 1 KB weight fragments per offset
+    static constexpr int RB = CLS == 0 ? 2 : 1;
+    static constexpr int NW = CLS == 0 ? (FR > 32 ? 8 : NB <= 4 && KCH == 1 ? 16 : 12) : CLS == 1 ? (FR > 32 ? 12 : 16) : CLS == 4 ? 4 : 8;
+    static constexpr int R = NW * RB * 16;
+    static constexpr int KS = KCH < 4 ? KCH : RB == 2 ? (NW >= 12 ? 2 : 4) : KCH;
+    static constexpr int SH = KCH / KS;  // steps per offset
+    static constexpr int RA = SH == 4 ? 3 : CLS == 0 && KCH == 3 && NBT <= 6 ? 2 : 1;
+    static constexpr int IX = R * kUK3 + 32;  // table entries (and the few the last steps read past them)
+    // offsets per weight group: as many as fit, in whole turns of the row ring where more than one fits
+    // (two workgroups per CU in the classes of one block of rows and 8 waves or fewer, if they fit)
+    static constexpr int UNIT = RA == 2 ? 3 : SH % (RA + 1) == 0 ? 1 : 2;
+    static constexpr int fit(int kb) {
+        const int n = (kb * 1024 - IX * 4) / (2 * FR * 1024);
+        return RA == 1 && n == 1 ? 1 : n > 14 ? 14 / UNIT * UNIT : n / UNIT * UNIT;
+    }
+    static constexpr int PH = CLS >= 2 && fit(80) >= 2 ? fit(80) : fit(160);
+    static constexpr bool valid = PH >= 1 && !(CLS == 1 && FR > 48) && !(CLS == 3 && NBS == NBL) && KCH * NBT <= 64;
+    static constexpr int per_cu = (IX * 4 + 2 * PH * FR * 1024) * 2 <= 160 * 1024 ? 2 : 1;
+};
+
+template <int DT, int KCH, int NB, int CLS>
+__global__ __launch_bounds__((64 * UnionTile<KCH, NB, CLS>::NW)) void k_conv_union(
     const int32_t* __restrict__ nbr, const int64_t* __restrict__ m_out_dev, int64_t m_cap,
-    const uint16_t* __restrict__ in, int Cin, int64_t in_rows, const uint4* __restrict__ wpack,
+    const uint16_t* __restrict__ in, int64_t in_rows, const uint4* __restrict__ wpack,
     const float* __restrict__ scale, const float* __restrict__ shift, int relu, const uint16_t* __restrict__ res,
     uint16_t* __restrict__ out) {
-    constexpr int K3 = kUK3;
-    constexpr int FR = KCH * NB;  // 1 KB weight fragments per offset
-    constexpr int Cout = NB * 16;
-    __shared__ __align__(16) uint4 wl[PH * FR * 64];
+    using T = UnionTile<KCH, NB, CLS>;
+    constexpr int K3 = kUK3, NBT = T::NBT, FR = T::FR, RB = T::RB, NW = T::NW, R = T::R, KS = T::KS, SH = T::SH;
+    constexpr int RA = T::RA, PH = T::PH, GS = PH * SH, NG = (K3 + PH - 1) / PH;  // steps per group, groups
+    constexpr int Cout = NB * 16, CT = NB / NBT;
+    constexpr int U = GS % (RA + 1) == 0 ? 1 : RA + 1;  // groups per turn of the loop: whole turns of the row ring
+    static_assert(GS >= RA, "the rows of the steps ahead are issued after the group's weight copies");
+    __shared__ __align__(16) uint4 wl[2][PH * FR * 64];
+    __shared__ __align__(16) int32_t ix[T::IX];
 
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, g = lane >> 4;
 
     // Workgroups are dispatched round-robin over the 8 XCDs (workgroup b to XCD
     // b % 8).  The row tiles that exist (from the live row count, not the
     // capacity the grid was sized for) are split into 8 consecutive ranges, one
-    // per XCD, so neighbouring tiles share an L2 and every XCD gets work.
+    // per XCD, so neighbouring tiles (and the channel slices of one tile) share
+    // an L2 and every XCD gets work.
     const int64_t m = clamp_rows(m_out_dev, m_cap);
-    constexpr int64_t rows_wg = (int64_t)NW * RB * 16;
-    const int64_t bid = blockIdx.x, x = bid % 8, seq = bid / 8;
-    const int64_t ga = (m + rows_wg - 1) / rows_wg, xq = ga / 8, xr = ga % 8;
+    const int64_t x = blockIdx.x % 8, seq = blockIdx.x / 8 / CT;
+    const int ct = (int)(blockIdx.x / 8 % CT);
+    const int64_t ga = (m + R - 1) / R, xq = ga / 8, xr = ga % 8;
     if (seq >= xq + (x < xr ? 1 : 0)) return;  // the whole workgroup
-    const int64_t wg = x * xq + (x < xr ? x : xr) + seq;
-    const int64_t blk0 = (wg * NW + wave) * RB;
+    const int64_t row0 = (x * xq + (x < xr ? x : xr) + seq) * R;
+    const int nrows = (int)(m - row0 < R ? m - row0 : R);
 
-    const __amdgpu_buffer_rsrc_t nb_rs = make_rsrc(nbr, (uint32_t)(m * K3 * 4));
-    const uint32_t row_bytes = (uint32_t)Cin * 2u;
+    // weights of offsets k0 .. k0 + nk - 1 (this workgroup's channel blocks) -> buffer buf
+    const i32x4* wsrc = (const i32x4*)wpack + ct * NBT * 64;
+    auto load_w = [&](int k0, int nk, int buf) __attribute__((always_inline)) {
+        for (int f = wave; f < nk * FR; f += NW) {
+            const int kk = f / NBT, nb = f - kk * NBT;  // kk = (k - k0) * KCH + kc
+            lds_dma_x4((uint64_t)(wsrc + ((int64_t)(k0 * KCH + kk) * NB + nb) * 64), (uint32_t)lane * 16u,
+                       __builtin_amdgcn_readfirstlane(lds_addr(&wl[buf][f * 64])));
+        }
+    };
+    load_w(0, K3 < PH ? K3 : PH, 0);
+    {
+        const int32_t* src = nbr + row0 * K3;
+        if (nrows == R && ((uintptr_t)src & 15) == 0) {
+            for (int e = tid; e < R * K3 / 4; e += 64 * NW) ((i32x4*)ix)[e] = ((const i32x4*)src)[e];
+        } else {
+            for (int e = tid; e < R * K3; e += 64 * NW) ix[e] = e < nrows * K3 ? src[e] : 0;
+        }
+    }
+    vm_wait<0>();
+    __syncthreads();
+
+    constexpr uint32_t row_bytes = KCH * 64u;
     const __amdgpu_buffer_rsrc_t in_rs = make_rsrc(in, (uint32_t)(in_rows * (int64_t)row_bytes));
     const uint32_t in_rows32 = (uint32_t)in_rows;
-
-    // nbr byte offset of (row of block b, offset 0) for this lane; rows past m read zeros
-    uint32_t nboff[RB];
-#pragma unroll
-    for (int b = 0; b < RB; ++b) {
-        const int64_t row = (blk0 + b) * 16 + r16;
-        nboff[b] = row < m ? (uint32_t)(row * K3 * 4) : kOutOfRange;
-    }
+    const int32_t* ixw = ix + (wave * RB * 16 + r16) * K3;
     // offsets present in each block (union over its 16 rows), wave-uniform
     uint32_t umask[RB];
 #pragma unroll
     for (int b = 0; b < RB; ++b) {
         uint32_t bits = 0;
 #pragma unroll
-        for (int k = 0; k < K3; k += 4) {
-            if (k + g < K3) {
-                const int v = __builtin_amdgcn_raw_buffer_load_b32(nb_rs, nboff[b] + (uint32_t)(k + g) * 4u, 0, 0);
-                bits |= (v > 0 ? 1u : 0u) << (k + g);
-            }
-        }
+        for (int k = 0; k < K3; k += 4)
+            if (k + g < K3) bits |= (ixw[b * 16 * K3 + k + g] > 0 ? 1u : 0u) << (k + g);
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) bits |= __shfl_xor(bits, d, 64);
         umask[b] = __builtin_amdgcn_readfirstlane(bits);
     }
-
-    auto load_nbr = [&](int k, int (&dst)[RB]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int b = 0; b < RB; ++b)
-            dst[b] = __builtin_amdgcn_raw_buffer_load_b32(nb_rs, nboff[b] + (uint32_t)k * 4u, 0, 0);
-    };
-    // gathered rows of offset kr (16-byte chunks g + 4 kc of row i)
-    // Every step issues the same RB * KCH loads, so the compiler's vmcnt waits
-    // are exact and a step waits for its own rows only, never for the rows it
-    // prefetches: a block without a neighbour at kr, or a lane whose row has
-    // none, loads from an out-of-range offset, which returns zeros and touches
-    // no memory.
-    auto load_rows = [&](int kr, const int (&nb1)[RB], i32x4 (&dst)[RB][KCH]) __attribute__((always_inline)) {
+    // gathered rows of (offset k, slab h): 16-byte chunks g + 4 (h KS + kc) of row i (stored as i + 1)
+    auto load_rows = [&](int k, int h, i32x4 (&dst)[RB][KS]) __attribute__((always_inline)) {
 #pragma unroll
         for (int b = 0; b < RB; ++b) {
-            const uint32_t i = (uint32_t)(nb1[b] - 1);  // stored as row + 1; 0 = absent
-            const bool have = ((umask[b] >> kr) & 1u) && i < in_rows32;
-            const uint32_t base = have ? i * row_bytes + (uint32_t)g * 16u : kOutOfRange;
+            const uint32_t i = (uint32_t)(ixw[b * 16 * K3 + k] - 1);
+            const uint32_t base = i < in_rows32 && k < K3 ? i * row_bytes + (uint32_t)g * 16u : kOutOfRange;
 #pragma unroll
-            for (int kc = 0; kc < KCH; ++kc)
-                dst[b][kc] = __builtin_amdgcn_raw_buffer_load_b128(in_rs, base + (uint32_t)kc * 64u, 0, 0);
+            for (int kc = 0; kc < KS; ++kc)
+                dst[b][kc] = __builtin_amdgcn_raw_buffer_load_b128(in_rs, base + (uint32_t)(h * KS + kc) * 64u, 0, 0);
         }
     };
 
-    int ns[kNAhead + 1][RB];         // neighbour indices of offset j in slot j % (kNAhead + 1)
-    i32x4 rs[kRAhead + 1][RB][KCH];  // gathered rows of offset j in slot j % (kRAhead + 1)
-#pragma unroll
-    for (int j = 0; j < kNAhead; ++j) load_nbr(j, ns[j]);
-#pragma unroll
-    for (int j = 0; j < kRAhead; ++j) load_rows(j, ns[j], rs[j]);
-
-    f32x4 acc[RB][NB];
+    f32x4 acc[RB][NBT];
 #pragma unroll
     for (int b = 0; b < RB; ++b)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[b][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int nb = 0; nb < NBT; ++nb) acc[b][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    const i32x4* wsrc = (const i32x4*)wpack;
-    static_for<0, K3>([&](auto kk) __attribute__((always_inline)) {
-        constexpr int k = decltype(kk)::value;
-        if constexpr (k % PH == 0) {
-            // a new phase: once every wave is done with the previous weights,
-            // copy W[k .. k+PH) into LDS
-            // (global->LDS copies, all issued before one wait: a copy through
-            // registers would wait for each fragment -- and every gather in
-            // flight -- in turn)
-            constexpr int nf = (K3 - k < PH ? K3 - k : PH) * FR;
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            const uint64_t gw = (uint64_t)(wsrc + (int64_t)k * FR * 64);
-            for (int f = wave; f < nf; f += NW)
-                lds_dma_x4(gw + (uint64_t)f * 1024u, (uint32_t)lane * 16u, lds_addr(wl + f * 64));
-            vm_wait<0>();
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
+    i32x4 rs[RA + 1][RB][KS];  // gathered rows of step j of a group in slot j % (RA + 1)
+#pragma unroll
+    for (int j = 0; j < RA; ++j) load_rows(j / SH, j % SH, rs[j]);
+    // group gi of offsets, whose first step's rows are in slot R0
+    auto group = [&](int gi, auto r0) __attribute__((always_inline)) {
+        constexpr int R0 = decltype(r0)::value;
+        const int k0 = gi * PH;
+        const i32x4* wbuf = (const i32x4*)wl[gi & 1] + lane;
+        if (gi + 1 < NG) {
+            // the first step's rows are here (the empty statements make the compiler wait for them), so the
+            // copies of the next weights delay no row that this step needs
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int kc = 0; kc < KS; ++kc) asm volatile("" : "+v"(rs[R0][b][kc]));
+            load_w(k0 + PH, K3 - k0 - PH < PH ? K3 - k0 - PH : PH, (gi + 1) & 1);
         }
-        if constexpr (k + kNAhead < K3) load_nbr(k + kNAhead, ns[(k + kNAhead) % (kNAhead + 1)]);
-        if constexpr (k + kRAhead < K3)
-            load_rows(k + kRAhead, ns[(k + kRAhead) % (kNAhead + 1)], rs[(k + kRAhead) % (kRAhead + 1)]);
-        const i32x4* wk = (const i32x4*)wl + (k % PH) * FR * 64;
-        uint32_t present = 0;
+        static_for<0, GS>([&](auto jj) __attribute__((always_inline)) {
+            constexpr int j = decltype(jj)::value, kp = j / SH, h = j % SH;
+            const int k = k0 + kp;
+            load_rows(k0 + (j + RA) / SH, (j + RA) % SH, rs[(R0 + j + RA) % (RA + 1)]);
+            if (K3 % PH == 0 || k < K3) {
+                uint32_t present = 0;
 #pragma unroll
-        for (int b = 0; b < RB; ++b) present |= ((umask[b] >> k) & 1u) << b;
-        if (present) {
+                for (int b = 0; b < RB; ++b) present |= ((umask[b] >> k) & 1u) << b;
+                if (present) {
+                    const i32x4* wk = wbuf + (kp * FR + h * KS * NBT) * 64;
 #pragma unroll
-            for (int kc = 0; kc < KCH; ++kc) {
-                i32x4 wf[NB];
+                    for (int kc = 0; kc < KS; ++kc) {
+                        i32x4 wf[NBT];
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) wf[nb] = wk[(kc * NB + nb) * 64 + lane];
+                        for (int nb = 0; nb < NBT; ++nb) wf[nb] = wk[(kc * NBT + nb) * 64];
 #pragma unroll
-                for (int b = 0; b < RB; ++b) {
-                    if ((present >> b) & 1u) {
+                        for (int b = 0; b < RB; ++b) {
+                            if (RB == 1 || ((present >> b) & 1u)) {
 #pragma unroll
-                        for (int nb = 0; nb < NB; ++nb)
-                            acc[b][nb] = mfma16x16x32<DT>(__builtin_bit_cast(uint4, wf[nb]),
-                                                          __builtin_bit_cast(uint4, rs[k % (kRAhead + 1)][b][kc]),
-                                                          acc[b][nb]);
+                                for (int nb = 0; nb < NBT; ++nb)
+                                    acc[b][nb] = mfma16x16x32<DT>(
+                                        __builtin_bit_cast(uint4, wf[nb]),
+                                        __builtin_bit_cast(uint4, rs[(R0 + j) % (RA + 1)][b][kc]), acc[b][nb]);
+                            }
+                        }
                     }
                 }
             }
+        });
+        if (gi + 1 < NG) {
+            // of what the wave has issued since the group's weight copies, only the rows of the RA steps
+            // ahead may be outstanding: the copies are complete
+            vm_wait<RA * RB * KS>();
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
         }
-    });
+    };
+#pragma clang loop unroll(disable)
+    for (int gt = 0; gt < NG; gt += U)
+        static_for<0, U>([&](auto u) __attribute__((always_inline)) {
+            constexpr int uu = decltype(u)::value;
+            if (U == 1 || gt + uu < NG) group(gt + uu, std::integral_constant<int, uu * GS % (RA + 1)>{});
+        });
 
     // epilogue: act(scale * acc + shift), 4 channels (8 bytes) per store
-    float sc[NB][4], sh[NB][4];
+    const int c0 = ct * NBT * 16 + 4 * g;
+    float sc[NBT][4], sh[NBT][4];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+    for (int nb = 0; nb < NBT; ++nb)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            sc[nb][e] = scale ? scale[nb * 16 + 4 * g + e] : 1.f;
-            sh[nb][e] = shift ? shift[nb * 16 + 4 * g + e] : 0.f;
+            sc[nb][e] = scale ? scale[c0 + nb * 16 + e] : 1.f;
+            sh[nb][e] = shift ? shift[c0 + nb * 16 + e] : 0.f;
         }
 #pragma unroll
     for (int b = 0; b < RB; ++b) {
-        const int64_t row = (blk0 + b) * 16 + r16;
-        if (row >= m) continue;
+        const int rr = (wave * RB + b) * 16 + r16;
+        if (rr >= nrows) continue;
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
+        for (int nb = 0; nb < NBT; ++nb) {
+            const int64_t at = (row0 + rr) * Cout + c0 + nb * 16;
             float y[4], rv[4] = {0.f, 0.f, 0.f, 0.f};
             if (res) {  // the residual input, same layout as the output
-                const uint2 u = *(const uint2*)(res + row * Cout + nb * 16 + 4 * g);
+                const uint2 u = *(const uint2*)(res + at);
                 rv[0] = from16<DT>(u.x & 0xFFFF);
                 rv[1] = from16<DT>(u.x >> 16);
                 rv[2] = from16<DT>(u.y & 0xFFFF);
@@ -209,7 +252,7 @@ __global__ __launch_bounds__(64 * NW) void k_conv_union(
             }
             const uint32_t lo = (uint32_t)to16<DT>(y[0]) | ((uint32_t)to16<DT>(y[1]) << 16);
             const uint32_t hi = (uint32_t)to16<DT>(y[2]) | ((uint32_t)to16<DT>(y[3]) << 16);
-            *(uint2*)(out + row * Cout + nb * 16 + 4 * g) = make_uint2(lo, hi);
+            *(uint2*)(out + at) = make_uint2(lo, hi);
         }
     }
 }
@@ -223,25 +266,58 @@ bool union_supported(int K3, int Cin, int Cout, int dt) {
     return width_ok(Cin) && width_ok(Cout);
 }
 
-// Launch shape per width: 11 waves of 2 blocks (352 rows per workgroup: a
-// ~9*10^4-voxel scan gives ~250 workgroups, one round over the 256 CUs with
-// nearly every CU busy), phases of as many offsets as fit in 128 KB of LDS.
-// 128 -> 128 takes one block per wave: two would not fit the 168 registers a
-// wave has at 11 waves per workgroup.
+// Which tile: whole rounds of workgroups over the 256 CUs times what one round takes.  A round of
+// workgroups of B blocks of 16 rows and FR weight fragments per offset measured about
+// 4 + 0.4 FR + B (0.1 + 0.28 KCH + 0.018 FR) us (96 -> 96: 21 us at 8 blocks, 31 at 16, 43 at 24; 32 -> 32:
+// 8 at 8, 15 at 32; 256 -> 256 in slices of 128 channels: 88 at 16, of 64: 60 at 16, of 32: 30 at 8), so a small tile wins while it still fits one round
+// and a large one when rounds are many.  The model only ranks: at 128 -> 128 on 18,631 rows it takes
+// 128-row tiles (32 us; 64-row tiles of half the channels 36, the former tile 38).
+// A device-side count (the block's voxels, of a capacity of all its points) is taken as 3/4 of the
+// capacity, about what a LiDAR sweep has.
+template <int KCH, int NB, int CLS>
+static double union_cost(int64_t rows) {
+    using T = UnionTile<KCH, NB, CLS>;
+    if constexpr (!T::valid) {
+        return 1e30;
+    } else {
+        const int64_t wgs = (rows + T::R - 1) / T::R * (NB / T::NBT), slots = 256 * T::per_cu;
+        // two workgroups on a CU share its pipes: half a round each beyond the fixed part
+        const double fixed = 4.0 + 0.4 * T::FR, work = T::R / 16 * (0.1 + 0.28 * KCH + 0.018 * T::FR);
+        const double full = fixed + work * T::per_cu, rounds = (double)(wgs / slots);
+        const int64_t rest = wgs % slots;
+        return rounds * full + (rest == 0 ? 0.0 : rest <= 256 ? fixed + work : full);
+    }
+}
+
+template <int DT, int KCH, int NB, int CLS>
+static void launch_union_tile(hipStream_t s, const ConvPlan& p, const void* in, int64_t in_rows, const void* wpack,
+                              const float* scale, const float* shift, int relu, void* out) {
+    using T = UnionTile<KCH, NB, CLS>;
+    if constexpr (T::valid) {
+        // a multiple of 8 workgroups: the kernel spreads the live tiles over the 8 XCDs
+        const unsigned grid = (unsigned)(((p.m_cap + T::R - 1) / T::R + 7) / 8 * 8 * (NB / T::NBT));
+        k_conv_union<DT, KCH, NB, CLS><<<grid, 64 * T::NW, 0, s>>>(p.nbr, p.m_out_dev, p.m_cap, (const uint16_t*)in,
+                                                                  in_rows, (const uint4*)wpack, scale, shift, relu,
+                                                                  (const uint16_t*)p.res, (uint16_t*)out);
+    }
+}
+
 template <int DT, int KCH, int NB>
 static void launch_union_c(hipStream_t s, const ConvPlan& p, const void* in, int64_t in_rows, const void* wpack,
                            const float* scale, const float* shift, int relu, void* out) {
-    constexpr int FR = KCH * NB;
-    // 256 channels in or out: 8 waves (256 registers each); 256 -> 256 holds one
-    // offset's 128 KB of weights per phase
-    constexpr int RB = FR >= 32 ? 1 : 2, NW = (NB >= 16 || KCH >= 8) ? 8 : 11;
-    constexpr int PH = (128 / FR) < kUK3 ? (128 / FR) : kUK3;  // 27, 14, 7, 4 for C -> C = 32, 64, 96, 128
-    constexpr int64_t rows_wg = (int64_t)NW * RB * 16;
-    // a multiple of 8 workgroups: the kernel spreads the live tiles over the 8 XCDs
-    const unsigned grid = (unsigned)(((p.m_cap + rows_wg - 1) / rows_wg + 7) / 8 * 8);
-    k_conv_union<DT, KCH, NB, RB, NW, PH><<<grid, 64 * NW, 0, s>>>(
-        p.nbr, p.m_out_dev, p.m_cap, (const uint16_t*)in, 32 * KCH, in_rows, (const uint4*)wpack, scale, shift, relu,
-        (const uint16_t*)p.res, (uint16_t*)out);
+    const int64_t rows = p.m_out_dev ? p.m_cap - p.m_cap / 4 : p.m_cap;
+    const double cost[5] = {union_cost<KCH, NB, 0>(rows), union_cost<KCH, NB, 1>(rows), union_cost<KCH, NB, 2>(rows),
+                            union_cost<KCH, NB, 3>(rows), union_cost<KCH, NB, 4>(rows)};
+    int c = 0;
+    for (int i = 1; i < 5; ++i)
+        if (cost[i] < cost[c]) c = i;
+    switch (c) {
+        case 0: launch_union_tile<DT, KCH, NB, 0>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 1: launch_union_tile<DT, KCH, NB, 1>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 2: launch_union_tile<DT, KCH, NB, 2>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 3: launch_union_tile<DT, KCH, NB, 3>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 4: launch_union_tile<DT, KCH, NB, 4>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+    }
 }
 
 template <int DT, int KCH>

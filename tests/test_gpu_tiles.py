@@ -1,0 +1,67 @@
+"""Kernels whose launch shape depends on the size of the call: every tile of the dispatch rules, at
+row counts just below, at and above the tile edges, against float64 on the same device."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def spv():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2007_16100_amd import spv as s
+    s.lib()
+    return s
+
+
+def rand(gen, *shape, dtype=torch.float32, std=1.0):
+    return (torch.randn(*shape, generator=gen, device="cuda") * std).to(dtype)
+
+
+def close16(got, ref, dtype):
+    """One rounding to the storage type (half an ulp: 2^-9 of a bf16, 2^-12 of an f16 value, taken
+    twice for values next to a rounding boundary) plus float32 sums of at most 27 * 256 terms of
+    order max|ref| / sqrt(terms), whose rounding is below 2^-14 of the largest output."""
+    ulp = 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -11
+    d = (got.double() - ref).abs()
+    assert torch.isfinite(got.float()).all()
+    assert bool((d <= ulp * ref.abs() + 2.0 ** -14 * ref.abs().max()).all()), float((d / ref.abs().max()).max())
+
+
+# rows around the tile edges (64, 128, 192, 256, 384 and 512 rows of a workgroup) and enough rows that
+# the rule takes each of its tiles; a table with and without 16-byte alignment; a device row count
+@pytest.mark.parametrize("cin,cout,dtype", [(32, 32, "bf16"), (96, 96, "f16"), (64, 128, "bf16"), (256, 96, "bf16"),
+                                            (128, 256, "f16"), (256, 256, "bf16")])
+@pytest.mark.parametrize("m", [1, 65, 511, 9001, 31_100, 70_001, 110_003])
+def test_conv_nbr_tiles(spv, cin, cout, dtype, m):
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(cin * 1000 + cout + m)
+    x, W = rand(gen, m, cin, dtype=dt), rand(gen, 27, cin, cout, dtype=dt, std=(27 * cin) ** -0.5)
+    sc, sh = torch.rand(cout, generator=gen, device="cuda") + 0.5, rand(gen, cout)
+    res = rand(gen, m, cout, dtype=dt)
+    # a fifth of the entries present, runs of rows without any at an offset (blocks that are skipped)
+    nbr = torch.randint(1, m + 1, (m, 27), generator=gen, device="cuda", dtype=torch.int32)
+    nbr[torch.rand(m, 27, generator=gen, device="cuda") < 0.8] = 0
+    nbr[m // 3: m // 2, 5:20] = 0
+    buf = torch.zeros(m * 27 + 1, dtype=torch.int32, device="cuda")
+    table = buf[1:].view(m, 27) if m % 2 else buf[:-1].view(m, 27)  # odd m: 4-byte aligned only
+    table.copy_(nbr)
+    live = m - m // 7
+    xd, ref = x.double(), torch.zeros(live, cout, dtype=torch.float64, device="cuda")
+    for k in range(27):
+        j = torch.nonzero(nbr[:live, k])[:, 0]
+        ref[j] += xd[(nbr[j, k] - 1).long()] @ W[k].double()
+    ref = (ref * sc + sh + res[:live].double()).relu()
+    ws = spv.Workspace.for_ops(max(m, 64), 256)
+    out = torch.full((m, cout), 7.0, dtype=dt, device="cuda")
+    P = spv.spv_pack_weights(W)
+    m_dev = torch.tensor([live], dtype=torch.int64, device="cuda")
+    spv.spv_sparse_conv_nbr_packed(ws, x, table, P, cout, m, m_out_dev=m_dev, scale=sc, shift=sh, relu=True, res=res,
+                                   out=out)
+    close16(out[:live], ref, dt)
+    assert bool((out[live:] == 7.0).all())  # rows past the count stay
+    again = torch.empty_like(out)
+    spv.spv_sparse_conv_nbr_packed(ws, x, table, P, cout, m, m_out_dev=m_dev, scale=sc, shift=sh, relu=True, res=res,
+                                   out=again)
+    assert torch.equal(again[:live].view(torch.int16), out[:live].view(torch.int16))
