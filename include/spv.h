@@ -171,7 +171,7 @@ spv_status spv_kernel_map(void* stream, void* ws, size_t ws_bytes,
  * Out: out [m_out_cap][Cout] (dt); rows < *m_out_dev are written (m_out_dev
  *      NULL = m_out_cap).
  * bf16/f16 with Cin % 8 == 0 and Cout % 16 == 0 run on MFMA; other shapes and
- * f32 run on a vector-ALU kernel with fp32 accumulation.
+ * f32 run on a float32 matrix-core kernel.
  */
 spv_status spv_sparse_conv(void* stream, void* ws, size_t ws_bytes,
                            const void* in, int64_t in_rows, int32_t Cin,
@@ -635,7 +635,7 @@ spv_status spv_voxel_lookup(void* stream, const void* ws, size_t ws_bytes, int64
  * spv_conv_kernel -- the kernel spv_sparse_conv (and its sliced / dgrad forms)
  * runs on for a shape and its sizes, as the call decides it on the host:
  * 0 = the neighbour-table MFMA kernel (3x3x3 maps), 1 = the tile MFMA kernel,
- * 2 = the vector-ALU kernel; -1 for arguments the calls reject.  The
+ * 2 = the float32 rows kernel; -1 for arguments the calls reject.  The
  * neighbour-table kernel addresses the input rows and its table with 32-bit
  * offsets: in_rows * Cin * 2 and m_out_cap * 27 * 4 must stay below
  * 0xFFFFE000, else a larger shape falls back to the next kernel.  Host only.

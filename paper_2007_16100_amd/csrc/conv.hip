@@ -21,7 +21,7 @@
 //   slice of the kernel map, multiplied 16 at a time and added into their
 //   output rows.
 //
-// A vector-ALU tile kernel covers fp32 and shapes the MFMA kernels do not take.
+// A float32 matrix-core kernel (k_conv_rows) covers fp32 and the shapes these two do not take.
 #include "conv_common.hpp"
 
 namespace spv {
@@ -30,7 +30,7 @@ namespace spv {
 // ---------------------------------------------------------------------------
 // plan
 // ---------------------------------------------------------------------------
-static int conv_tile_rows(int Cin, int Cout, int dt);
+static int conv_tile_rows(int Cin, int Cout, int dt, int64_t m_cap);
 
 // The boundary array is sized for the smallest tile (16 rows) and the neighbour
 // table is reserved for every 3x3x3 plan, so the workspace size does not depend
@@ -42,7 +42,7 @@ void plan_conv_ws(Arena& a, ConvPlan& p, int64_t m_out_cap, int K3, int Cin, int
     // decided once here: launch_conv_plan builds what this kernel reads
     // (neighbour table or tile bounds) and launch_conv_run runs it
     p.use_union = conv_kernel_choice(K3, Cin, Cout, dt, p.m_cap, in_rows, 0, sparse_transposed) == kConvUnion ? 1 : 0;
-    p.tile_rows = conv_tile_rows(Cin, Cout, dt);
+    p.tile_rows = conv_tile_rows(Cin, Cout, dt, p.m_cap);
     p.ntile_cap = (p.m_cap + p.tile_rows - 1) / p.tile_rows;
     p.bnd = a.take<int32_t>((size_t)K3 * ((p.m_cap + kChunk - 1) / kChunk + 1));
     // reserved for every 3x3x3 plan, so that a workspace sized for one dtype / width serves all
@@ -478,53 +478,175 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
 }
 
 // ---------------------------------------------------------------------------
-// vector-ALU tile kernel (f32, or shapes the MFMA kernel does not take):
-// 64 output channels per workgroup (grid.y), 4 pair lanes; LDS accumulator
-// [T][64]; a barrier between offsets keeps the updates of one row ordered.
+// float32 rows kernel (f32, or shapes the 16-bit MFMA kernels do not take)
 // ---------------------------------------------------------------------------
-template <int DT>
-__global__ __launch_bounds__(256) void k_conv_tile_valu(ConvPlan p, const void* in, int Cin, int64_t in_rows,
-                                                        const int32_t* pairs, int64_t pair_bound, int transposed,
-                                                        const void* W,
-                                                        const float* scale, const float* shift, int relu, void* out,
-                                                        int Cout) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    float* acc = (float*)smem;
-    const int T = p.tile_rows, K3 = p.K3;
+// A workgroup computes T = 16 RB output rows times NBT blocks of 16 output channels (grid.y covers
+// the others).  Its four waves share the map's offsets (wave w takes those with k % 4 = w), so that
+// even a cloud of a thousand voxels gives every CU work and no wave more than 7 offsets; the four
+// partial sums are added in wave order, a fixed association.  The tile's pairs become a table
+// ix[k][row] in LDS; offsets that none of the rows has are skipped.
+//
+// Products run on v_mfma_f32_16x16x4_f32 (float32 multiply and add; 16-bit values widen exactly) as
+// D = W^T G^T: of a slab of 16 input channels, lane (r16, g) holds channels 4g .. 4g + 3 of gathered
+// row r16 (one 16-byte load in float32) and of output channel r16, an element of each per
+// instruction.  The loads of the next step are issued before the products of this one.
+//
+// It is bound by those loads' latency on few rows and by reading W from L2 once per tile on many.  The
+// vector-ALU kernel it replaced walked each pair's input channels one load at a time: a block of two
+// 16 -> 16 convs on a 2,000-point cloud took 1,100 us, of which they were 925, and takes 101.
+template <int DT, bool VEC>
+__device__ __forceinline__ f32x4 ld_feat4(const void* p, int64_t row, int C, int c) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (VEC) {  // C % 4 == 0: whole pieces, aligned to four elements
+        if (c < C) {
+            if constexpr (DT == SPV_F32) {
+                v = *(const f32x4*)((const float*)p + row * C + c);
+            } else {
+                const uint2 u = *(const uint2*)((const uint16_t*)p + row * C + c);
+                v = f32x4{from16<DT>(u.x & 0xFFFF), from16<DT>(u.x >> 16), from16<DT>(u.y & 0xFFFF),
+                          from16<DT>(u.y >> 16)};
+            }
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (c + e < C) v[e] = ld_feat<DT>(p, row * C + c + e);
+    }
+    return v;
+}
+
+template <int DT, int RB, int NBT, bool VEC>
+__global__ __launch_bounds__(256) void k_conv_rows(ConvPlan p, const void* in, int Cin, int64_t in_rows,
+                                                   const int32_t* pairs, int64_t pair_bound, int transposed,
+                                                   const void* W, const float* scale, const float* shift, int relu,
+                                                   void* out, int Cout) {
+    constexpr int T = 16 * RB, CW = 16 * NBT, RS = CW + 4;
+    __shared__ int32_t ix[kMaxK3][T];  // input row + 1 of (offset, output row), 0 = none
+    __shared__ __align__(16) float red[4][T][RS];
+    const int K3 = p.K3, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, g = lane >> 4;
     const int64_t t = blockIdx.x;
     const int64_t m = clamp_rows(p.m_out_dev, p.m_cap);
     const int64_t nt = (m + T - 1) / T;
     if (t >= nt) return;
     const int64_t row0 = t * T;
     const int rows = (int)((m - row0) < T ? (m - row0) : T);
-    const int cl = threadIdx.x & 63, rl = threadIdx.x >> 6;
-    const int col = blockIdx.y * 64 + cl;
-    const bool cok = col < Cout;
-    for (int e = threadIdx.x; e < T * 64; e += blockDim.x) acc[e] = 0.f;
+    const int col0 = blockIdx.y * CW;
+
+    for (int e = tid; e < K3 * T; e += 256) ix[e / T][e % T] = 0;
     __syncthreads();
     const int isel = transposed ? 1 : 0;
     const int64_t bs = p.ntile_cap + 1;
-    const int64_t ldc = p.w_ldc > 0 ? p.w_ldc : Cout, ldk = p.w_ldk > 0 ? p.w_ldk : (int64_t)Cin * Cout;
-    const int64_t ldcol = p.w_ldcol > 0 ? p.w_ldcol : 1;
-    for (int k = 0; k < K3; ++k) {
+    for (int e = tid; e < K3 * T; e += 256) {
+        // at most T pairs of an offset have their output row in the tile (a map with more is not a
+        // kernel map, which the plan reports); clamped into the pair list
+        const int k = e / T;
         int64_t lo = p.bnd[k * bs + t], hi = p.bnd[k * bs + t + 1];
         lo = lo < 0 ? 0 : (lo > pair_bound ? pair_bound : lo);
         hi = hi < lo ? lo : (hi > pair_bound ? pair_bound : hi);
-        for (int64_t pi = lo + rl; pi < hi; pi += 4) {
-            const int32_t i = pairs[2 * pi + isel];
-            const int64_t o = (int64_t)pairs[2 * pi + 1 - isel] - row0;
-            if (!cok || o < 0 || o >= rows || i < 0 || i >= in_rows) continue;
-            float s = 0.f;
-            for (int ci = 0; ci < Cin; ++ci)
-                s += ld_feat<DT>(in, (int64_t)i * Cin + ci) * ld_feat<DT>(W, k * ldk + ci * ldc + col * ldcol);
-            acc[o * 64 + cl] += s;
-        }
-        __syncthreads();
+        const int64_t pi = lo + e % T;
+        if (pi >= hi) continue;
+        const int32_t i = pairs[2 * pi + isel];
+        const int64_t o = (int64_t)pairs[2 * pi + 1 - isel] - row0;
+        if (o >= 0 && o < rows && i >= 0 && i < in_rows) ix[k][o] = i + 1;
     }
-    if (!cok) return;
-    const float sc = scale ? scale[col] : 1.f, sh = shift ? shift[col] : 0.f;
-    for (int r = rl; r < rows; r += 4) {
-        float y = acc[r * 64 + cl] * sc + sh;
+    __syncthreads();
+
+    const int64_t ldc = p.w_ldc > 0 ? p.w_ldc : Cout, ldk = p.w_ldk > 0 ? p.w_ldk : (int64_t)Cin * Cout;
+    const int64_t ldcol = p.w_ldcol > 0 ? p.w_ldcol : 1;
+    const int ns = (Cin + 15) / 16;  // slabs per offset
+
+    f32x4 acc[RB][NBT];
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int nb = 0; nb < NBT; ++nb) acc[b][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // this wave's offsets that some row has
+    uint32_t todo = 0;
+    for (int k = wave; k < K3; k += 4) {
+        int any = 0;
+        for (int b = 0; b < RB; ++b) any |= ix[k][b * 16 + r16];
+        if (__ballot(any != 0)) todo |= 1u << k;
+    }
+    f32x4 x0[RB], w0[NBT], x1[RB], w1[NBT];
+    auto load = [&](int k, int sl, f32x4 (&x)[RB], f32x4 (&w)[NBT]) __attribute__((always_inline)) {
+        const int c = sl * 16 + 4 * g;
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+            const int32_t i = ix[k][b * 16 + r16];
+            x[b] = i > 0 ? ld_feat4<DT, VEC>(in, i - 1, Cin, c) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int nb = 0; nb < NBT; ++nb) {
+            const int col = col0 + nb * 16 + r16;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                w[nb][e] = (c + e < Cin && col < Cout) ? ld_feat<DT>(W, k * ldk + (c + e) * ldc + col * ldcol) : 0.f;
+        }
+    };
+    // A row without this offset holds zeros, which add nothing unless a weight is infinite or NaN: then
+    // the products are formed apart and added to the rows that have it.
+    auto multiply = [&](int kk, const f32x4 (&x)[RB], const f32x4 (&w)[NBT]) __attribute__((always_inline)) {
+        bool odd = false;
+#pragma unroll
+        for (int nb = 0; nb < NBT; ++nb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) odd = odd || !(fabsf(w[nb][e]) <= 3.402823466e38f);
+        if (__ballot(odd)) {
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int nb = 0; nb < NBT; ++nb) {
+                    f32x4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        d = __builtin_amdgcn_mfma_f32_16x16x4f32(w[nb][e], x[b][e], d, 0, 0, 0);
+                    if (ix[kk][b * 16 + r16] > 0) acc[b][nb] += d;
+                }
+            return;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int nb = 0; nb < NBT; ++nb)
+                    acc[b][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[nb][e], x[b][e], acc[b][nb], 0, 0, 0);
+    };
+    const int steps = __builtin_popcount(todo) * ns;
+    int k = todo ? __builtin_ctz(todo) : 0, sl = 0;
+    auto next = [&]() {  // the step after (k, sl); stays on the last one
+        if (++sl == ns) {
+            const uint32_t rest = todo & ~((2u << k) - 1u);
+            sl = rest ? 0 : ns - 1;
+            k = rest ? __builtin_ctz(rest) : k;
+        }
+    };
+    if (steps > 0) load(k, sl, x0, w0);
+    for (int st = 0; st < steps; st += 2) {
+        const int k0 = k;
+        next();
+        const int k1 = k;
+        if (st + 1 < steps) load(k1, sl, x1, w1);
+        multiply(k0, x0, w0);
+        if (st + 1 < steps) {
+            next();
+            if (st + 2 < steps) load(k, sl, x0, w0);
+            multiply(k1, x1, w1);
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int nb = 0; nb < NBT; ++nb) *(f32x4*)&red[wave][b * 16 + r16][nb * 16 + 4 * g] = acc[b][nb];
+    __syncthreads();
+    for (int e = tid; e < rows * CW; e += 256) {
+        const int r = e / CW, c = e % CW, col = col0 + c;
+        if (col >= Cout) continue;
+        const float a = (red[0][r][c] + red[1][r][c]) + (red[2][r][c] + red[3][r][c]);
+        float y = a * (scale ? scale[col] : 1.f) + (shift ? shift[col] : 0.f);
         if (p.res) y += ld_feat<DT>(p.res, (row0 + r) * Cout + col);
         if (relu) y = fmaxf(y, 0.f);
         st_feat<DT>(out, (row0 + r) * Cout + col, y);
@@ -557,8 +679,10 @@ bool conv_mfma_supported(int Cin, int Cout, int dt) {
     return NB / conv_nbw(conv_kch(Cin), NB) <= 8;  // at most 8 waves per workgroup
 }
 
-static int conv_tile_rows(int Cin, int Cout, int dt) {
-    if (!conv_mfma_supported(Cin, Cout, dt)) return 128;
+static int conv_tile_rows(int Cin, int Cout, int dt, int64_t m_cap) {
+    // k_conv_rows: 16 rows per workgroup until those give four workgroups per CU, then more rows, which
+    // read W less often
+    if (!conv_mfma_supported(Cin, Cout, dt)) return m_cap <= 16 * 1024 ? 16 : m_cap <= 32 * 1024 ? 32 : 64;
     const int KCH = conv_kch(Cin), NB = Cout / 16, NBW = conv_nbw(KCH, NB), NW = NB / NBW;
     // the largest tile with which two workgroups share a compute unit's 160 KB of LDS
     for (int T = 128; T > 16; T >>= 1)
@@ -630,6 +754,45 @@ static void launch_tile(hipStream_t s, const ConvPlan& p, const void* in, int Ci
     }
 }
 
+template <int DT, int RB, int NBT>
+static void launch_rows_c(hipStream_t s, const ConvPlan& p, const void* in, int Cin, int64_t in_rows,
+                          const int32_t* pairs, int64_t pair_bound, int transposed, const void* W, const float* scale,
+                          const float* shift, int relu, void* out, int Cout) {
+    const dim3 grid((unsigned)(p.ntile_cap > 0 ? p.ntile_cap : 1), (unsigned)((Cout + 16 * NBT - 1) / (16 * NBT)));
+    if (Cin % 4 == 0)
+        k_conv_rows<DT, RB, NBT, true><<<grid, 256, 0, s>>>(p, in, Cin, in_rows, pairs, pair_bound, transposed, W,
+                                                            scale, shift, relu, out, Cout);
+    else
+        k_conv_rows<DT, RB, NBT, false><<<grid, 256, 0, s>>>(p, in, Cin, in_rows, pairs, pair_bound, transposed, W,
+                                                             scale, shift, relu, out, Cout);
+}
+
+// channel blocks per workgroup: up to 4, so that a gathered row is read once per 64 output channels
+template <int DT>
+static void launch_rows(hipStream_t s, const ConvPlan& p, const void* in, int Cin, int64_t in_rows,
+                        const int32_t* pairs, int64_t pair_bound, int transposed, const void* W, const float* scale,
+                        const float* shift, int relu, void* out, int Cout) {
+#define SPV_ROWS_CASE(T)                                                                                              \
+    case T:                                                                                                           \
+        if (Cout <= 16)                                                                                               \
+            launch_rows_c<DT, T / 16, 1>(s, p, in, Cin, in_rows, pairs, pair_bound, transposed, W, scale, shift, relu, \
+                                         out, Cout);                                                                  \
+        else if (Cout <= 32)                                                                                          \
+            launch_rows_c<DT, T / 16, 2>(s, p, in, Cin, in_rows, pairs, pair_bound, transposed, W, scale, shift, relu, \
+                                         out, Cout);                                                                  \
+        else                                                                                                          \
+            launch_rows_c<DT, T / 16, 4>(s, p, in, Cin, in_rows, pairs, pair_bound, transposed, W, scale, shift, relu, \
+                                         out, Cout);                                                                  \
+        break;
+    switch (p.tile_rows) {
+        SPV_ROWS_CASE(16)
+        SPV_ROWS_CASE(32)
+        SPV_ROWS_CASE(64)
+        SPV_ROWS_CASE(128)  // the tile kernel's plan, where the pair list is too long for that kernel
+    }
+#undef SPV_ROWS_CASE
+}
+
 PackJob conv_pack_job(int K3, const void* W, void* wpack, int Cin, int Cout, int dt, int ldc, int64_t ldk,
                       int ldcol) {
     PackJob q{(const uint16_t*)W, (uint4*)wpack, K3, Cin, Cout, 0, 0, 0, ldc > 0 ? ldc : Cout,
@@ -686,17 +849,12 @@ void launch_conv_run(hipStream_t s, const ConvPlan& p, const void* in, int Cin, 
                                  out, Cout);
         return;
     }
-    dim3 grid((unsigned)(p.ntile_cap > 0 ? p.ntile_cap : 1), (unsigned)((Cout + 63) / 64));
-    const size_t lds = (size_t)p.tile_rows * 64 * 4;
     if (dt == SPV_F32)
-        k_conv_tile_valu<SPV_F32><<<grid, 256, lds, s>>>(p, in, Cin, in_rows, pairs, pair_bound, transposed, W, scale,
-                                                         shift, relu, out, Cout);
+        launch_rows<SPV_F32>(s, p, in, Cin, in_rows, pairs, pair_bound, transposed, W, scale, shift, relu, out, Cout);
     else if (dt == SPV_BF16)
-        k_conv_tile_valu<SPV_BF16><<<grid, 256, lds, s>>>(p, in, Cin, in_rows, pairs, pair_bound, transposed, W,
-                                                          scale, shift, relu, out, Cout);
+        launch_rows<SPV_BF16>(s, p, in, Cin, in_rows, pairs, pair_bound, transposed, W, scale, shift, relu, out, Cout);
     else
-        k_conv_tile_valu<SPV_F16><<<grid, 256, lds, s>>>(p, in, Cin, in_rows, pairs, pair_bound, transposed, W,
-                                                         scale, shift, relu, out, Cout);
+        launch_rows<SPV_F16>(s, p, in, Cin, in_rows, pairs, pair_bound, transposed, W, scale, shift, relu, out, Cout);
 }
 
 }  // namespace spv

@@ -1,5 +1,5 @@
 // conv_common.hpp -- helpers shared by the sparse-convolution kernels
-// (conv.hip: plan, tile and vector-ALU kernels; conv_union.hip: the 3x3x3
+// (conv.hip: plan, tile and float32 kernels; conv_union.hip: the 3x3x3
 // neighbour-table kernel).
 #pragma once
 

@@ -253,7 +253,7 @@ __device__ inline void clear_nbr_upper(int32_t* nbr, int64_t v) {
 struct ConvPlan {
     int64_t m_cap;      // output row capacity
     int K3;
-    int use_union;      // 1: neighbour-table kernel, 0: tile kernel (or vector ALU)
+    int use_union;      // 1: neighbour-table kernel, 0: tile kernel (or float32 rows kernel)
     int tile_rows;      // output rows per tile (power of two)
     int64_t ntile_cap;  // ceil(m_cap / tile_rows)
     int32_t* bnd;       // [K3][ntile_cap + 1]
@@ -263,7 +263,7 @@ struct ConvPlan {
     // residual input [m][Cout] of the storage type (nullptr = none), added after
     // scale and shift and before the activation; it must not alias the output
     const void* res = nullptr;
-    // W strides in elements for the vector-ALU kernel, which reads W itself
+    // W strides in elements for the float32 rows kernel, which reads W itself
     // (0: a dense [K3][Cin][Cout] tensor)
     int w_ldc = 0;
     int64_t w_ldk = 0;

@@ -702,7 +702,7 @@ def spv_voxel_lookup(ws: Workspace, n: int, qcoords: torch.Tensor) -> torch.Tens
 
 def spv_conv_kernel(K3: int, Cin: int, Cout: int, dtype: torch.dtype, in_rows: int, m_out_cap: int,
                     pair_cap: int, transposed: bool = False) -> int:
-    """Host query: 0 neighbour-table MFMA, 1 tile MFMA, 2 vector ALU, -1 rejected."""
+    """Host query: 0 neighbour-table MFMA, 1 tile MFMA, 2 float32 rows, -1 rejected."""
     return lib().spv_conv_kernel(K3, Cin, Cout, _DT[dtype], in_rows, m_out_cap, pair_cap, int(transposed))
 
 

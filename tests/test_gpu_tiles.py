@@ -65,3 +65,36 @@ def test_conv_nbr_tiles(spv, cin, cout, dtype, m):
     spv.spv_sparse_conv_nbr_packed(ws, x, table, P, cout, m, m_out_dev=m_dev, scale=sc, shift=sh, relu=True, res=res,
                                    out=again)
     assert torch.equal(again[:live].view(torch.int16), out[:live].view(torch.int16))
+
+
+# 16, 32 and 64 rows of a workgroup and the capacities at which the rule changes between them; widths
+# that are no multiple of 4 (element loads), of 16, and over one workgroup's 64 output channels
+@pytest.mark.parametrize("cin,cout,dtype", [(16, 16, "f32"), (5, 19, "f32"), (48, 70, "f32"), (6, 9, "bf16"),
+                                            (20, 33, "f16")])
+@pytest.mark.parametrize("m", [1, 17, 1500, 16_385, 32_769])
+def test_conv_rows_tiles(spv, cin, cout, dtype, m):
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(cin * 1000 + cout + m)
+    side = int((4 * m) ** (1 / 3)) + 1
+    cell = torch.randperm(side ** 3, generator=gen, device="cuda")[:m].sort().values
+    m = len(cell)
+    coords = torch.stack([torch.zeros_like(cell), cell // side ** 2, cell // side % side, cell % side], 1).int()
+    ws = spv.Workspace.for_ops(max(m, 64), 256)
+    km = spv.spv_kernel_map(ws, coords.contiguous())
+    assert spv.spv_conv_kernel(27, cin, cout, dt, m, m, km.total) == 2
+    x, W = rand(gen, m, cin, dtype=dt), rand(gen, 27, cin, cout, dtype=dt, std=(27 * cin) ** -0.5)
+    W[4, 0, 0] = float("inf")  # reaches the rows that have offset 4 and no other
+    res = rand(gen, m, cout, dtype=dt)
+    out = spv.spv_sparse_conv_sliced(ws, x, km.off, km.pairs, W, cin, cout, m, res=res)
+    assert spv.spv_status_check(ws) == 0
+    off, pairs = km.off.tolist(), km.pairs.long()
+    ref, xd = res.double(), x.double()
+    for k in range(27):
+        i, j = pairs[off[k]: off[k + 1]].T
+        ref[j] += xd[i] @ W[k].double()
+    fine = torch.isfinite(ref)
+    assert bool((fine == torch.isfinite(out.double())).all())
+    d, scale = (out.double() - ref)[fine].abs(), ref[fine].abs()
+    # half an ulp of the storage type (twice) and float32 sums of 27 * 48 terms at most
+    ulp = {"f32": 2.0 ** -23, "bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype]
+    assert bool((d <= ulp * scale + 2.0 ** -18 * scale.max()).all()), float((d / scale.max()).max())
