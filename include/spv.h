@@ -634,7 +634,9 @@ spv_status spv_voxel_lookup(void* stream, const void* ws, size_t ws_bytes, int64
 /*
  * spv_conv_kernel -- the kernel spv_sparse_conv (and its sliced / dgrad forms)
  * runs on for a shape and its sizes, as the call decides it on the host:
- * 0 = the neighbour-table MFMA kernel (3x3x3 maps), 1 = the tile MFMA kernel,
+ * 0 = the neighbour-table MFMA kernel (3x3x3 maps), 1 = the MFMA kernels of
+ * the other maps and widths (2x2x2 maps by output at the neighbour-table
+ * widths run on a table of 8, the rest on tiles of pairs),
  * 2 = the float32 rows kernel; -1 for arguments the calls reject.  The
  * neighbour-table kernel addresses the input rows and its table with 32-bit
  * offsets: in_rows * Cin * 2 and m_out_cap * 27 * 4 must stay below

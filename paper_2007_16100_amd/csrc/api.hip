@@ -376,10 +376,14 @@ static spv_status sparse_conv_call(void* stream, void* ws, size_t ws_bytes, cons
     // through for every block: the tile kernel, which only visits pairs, takes
     // it.  A transposed map with as many inputs as outputs (a submanifold map
     // read backwards, as in the input gradient) is as dense as the forward one.
-    const bool sparse_tr = transposed && in_rows != m_out_cap;
+    bool sparse_tr = transposed && in_rows != m_out_cap;
     ConvLayout L;
-    if (need(layout_conv(nullptr, 0, m_out_cap, K3, Cin, Cout, dt, L, in_rows, sparse_tr), ws_bytes))
-        return SPV_ERR_CAPACITY;
+    if (need(layout_conv(nullptr, 0, m_out_cap, K3, Cin, Cout, dt, L, in_rows, sparse_tr), ws_bytes)) {
+        // a workspace without room for a 2x2x2 map's table: the pairs themselves (the tile kernel)
+        sparse_tr = true;
+        if (K3 != 8 || need(layout_conv(nullptr, 0, m_out_cap, K3, Cin, Cout, dt, L, in_rows, true), ws_bytes))
+            return SPV_ERR_CAPACITY;
+    }
     layout_conv(ws, ws_bytes, m_out_cap, K3, Cin, Cout, dt, L, in_rows, sparse_tr);
     hipStream_t s = (hipStream_t)stream;
     if (m_out_cap == 0) return clear_status_only(s, ws);

@@ -31,6 +31,7 @@ namespace spv {
 // plan
 // ---------------------------------------------------------------------------
 static int conv_tile_rows(int Cin, int Cout, int dt, int64_t m_cap);
+static bool conv_fits_buffers(int64_t in_rows, int Cin, int64_t pair_bound);
 
 // The boundary array is sized for the smallest tile (16 rows) and the neighbour
 // table is reserved for every 3x3x3 plan, so the workspace size does not depend
@@ -42,11 +43,16 @@ void plan_conv_ws(Arena& a, ConvPlan& p, int64_t m_out_cap, int K3, int Cin, int
     // decided once here: launch_conv_plan builds what this kernel reads
     // (neighbour table or tile bounds) and launch_conv_run runs it
     p.use_union = conv_kernel_choice(K3, Cin, Cout, dt, p.m_cap, in_rows, 0, sparse_transposed) == kConvUnion ? 1 : 0;
+    // a 2x2x2 map by output: the neighbour-table kernel on a table of 8 (64 -> 128 onto 50k voxels of a
+    // sweep: 65 us on the tile kernel's pairs)
+    if (K3 == 8 && !sparse_transposed && union_supported(27, Cin, Cout, dt) && p.m_cap * 32 <= (int64_t)0xFFFFE000 &&
+        conv_fits_buffers(in_rows, Cin, 0))
+        p.use_union = 1;
     p.tile_rows = conv_tile_rows(Cin, Cout, dt, p.m_cap);
     p.ntile_cap = (p.m_cap + p.tile_rows - 1) / p.tile_rows;
     p.bnd = a.take<int32_t>((size_t)K3 * ((p.m_cap + kChunk - 1) / kChunk + 1));
     // reserved for every 3x3x3 plan, so that a workspace sized for one dtype / width serves all
-    p.nbr = K3 == 27 ? a.take<int32_t>((size_t)p.m_cap * K3) : nullptr;
+    p.nbr = K3 == 27 || p.use_union ? a.take<int32_t>((size_t)p.m_cap * K3) : nullptr;
     p.h = nullptr;
     p.m_out_dev = nullptr;
 }

@@ -16,7 +16,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // ---------------------------------------------------------------------------
-// neighbour-table kernel (3x3x3 maps)
+// neighbour-table kernel (3x3x3 maps, and the 2x2x2 stride-2 maps by output)
 // ---------------------------------------------------------------------------
 // A workgroup of NW waves computes R = 16 RB NW output rows times NBT blocks of 16 output channels
 // (NB / NBT workgroups share the rows).  A wave owns RB blocks of 16 rows; the accumulators of a
@@ -42,10 +42,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 // blocks with no neighbour at k skip their products.  The copies the compiler does not see are
 // issued after the group's first rows have arrived and waited for by count before the barrier: the
 // loads issued after them are the rows of the steps ahead.
-constexpr int kUK3 = 27;
-
 // shape of a workgroup's tile; valid when it fits in LDS and in the registers of a wave
-template <int KCH, int NB, int CLS>
+template <int K3, int KCH, int NB, int CLS>
 struct UnionTile {
     // output-channel blocks of a workgroup: all of them (at most 8) in the classes for many rows, at
     // most half of them in the classes that spread few rows over the chip
@@ -58,28 +56,29 @@ struct UnionTile {
     static constexpr int R = NW * RB * 16;
     static constexpr int KS = KCH < 4 ? KCH : RB == 2 ? (NW >= 12 ? 2 : 4) : KCH;
     static constexpr int SH = KCH / KS;  // steps per offset
-    static constexpr int RA = SH == 4 ? 3 : CLS == 0 && KCH == 3 && NBT <= 6 ? 2 : 1;
-    static constexpr int IX = R * kUK3 + 32;  // table entries (and the few the last steps read past them)
+    static constexpr int RA = SH == 4 ? 3 : K3 == 27 && CLS == 0 && KCH == 3 && NBT <= 6 ? 2 : 1;
+    static constexpr int IX = R * K3 + 32;  // table entries (and the few the last steps read past them)
     // offsets per weight group: as many as fit, in whole turns of the row ring where more than one fits
     // (two workgroups per CU in the classes of one block of rows and 8 waves or fewer, if they fit)
     static constexpr int UNIT = RA == 2 ? 3 : SH % (RA + 1) == 0 ? 1 : 2;
     static constexpr int fit(int kb) {
         const int n = (kb * 1024 - IX * 4) / (2 * FR * 1024);
-        return RA == 1 && n == 1 ? 1 : n > 14 ? 14 / UNIT * UNIT : n / UNIT * UNIT;
+        const int most = K3 == 8 ? 4 : 14;
+        return RA == 1 && n == 1 ? 1 : n > most ? most / UNIT * UNIT : n / UNIT * UNIT;
     }
     static constexpr int PH = CLS >= 2 && fit(80) >= 2 ? fit(80) : fit(160);
     static constexpr bool valid = PH >= 1 && !(CLS == 1 && FR > 48) && !(CLS == 3 && NBS == NBL) && KCH * NBT <= 64;
     static constexpr int per_cu = (IX * 4 + 2 * PH * FR * 1024) * 2 <= 160 * 1024 ? 2 : 1;
 };
 
-template <int DT, int KCH, int NB, int CLS>
-__global__ __launch_bounds__((64 * UnionTile<KCH, NB, CLS>::NW)) void k_conv_union(
+template <int DT, int K3, int KCH, int NB, int CLS>
+__global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW)) void k_conv_union(
     const int32_t* __restrict__ nbr, const int64_t* __restrict__ m_out_dev, int64_t m_cap,
     const uint16_t* __restrict__ in, int64_t in_rows, const uint4* __restrict__ wpack,
     const float* __restrict__ scale, const float* __restrict__ shift, int relu, const uint16_t* __restrict__ res,
     uint16_t* __restrict__ out) {
-    using T = UnionTile<KCH, NB, CLS>;
-    constexpr int K3 = kUK3, NBT = T::NBT, FR = T::FR, RB = T::RB, NW = T::NW, R = T::R, KS = T::KS, SH = T::SH;
+    using T = UnionTile<K3, KCH, NB, CLS>;
+    constexpr int NBT = T::NBT, FR = T::FR, RB = T::RB, NW = T::NW, R = T::R, KS = T::KS, SH = T::SH;
     constexpr int RA = T::RA, PH = T::PH, GS = PH * SH, NG = (K3 + PH - 1) / PH;  // steps per group, groups
     constexpr int Cout = NB * 16, CT = NB / NBT;
     constexpr int U = GS % (RA + 1) == 0 ? 1 : RA + 1;  // groups per turn of the loop: whole turns of the row ring
@@ -220,6 +219,44 @@ __global__ __launch_bounds__((64 * UnionTile<KCH, NB, CLS>::NW)) void k_conv_uni
             if (U == 1 || gt + uu < NG) group(gt + uu, std::integral_constant<int, uu * GS % (RA + 1)>{});
         });
 
+    if constexpr (K3 == 8) {
+        // Rows without an offset added zeros times its weights, which is nothing unless a weight is infinite
+        // or NaN: a row that is not finite is summed again over its own offsets only (half of a block's rows
+        // lack an offset that the block has, so this must not spread to them).
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+            bool odd = false;
+#pragma unroll
+            for (int nb = 0; nb < NBT; ++nb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) odd = odd || !(fabsf(acc[b][nb][e]) <= 3.402823466e38f);
+            if (!__ballot(odd)) continue;
+            f32x4 sum[NBT];
+#pragma unroll
+            for (int nb = 0; nb < NBT; ++nb) sum[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int k = 0; k < K3; ++k) {
+                const uint32_t i = (uint32_t)(ixw[b * 16 * K3 + k] - 1);
+                const bool have = i < in_rows32;
+                const uint32_t base = have ? i * row_bytes + (uint32_t)g * 16u : kOutOfRange;
+#pragma unroll
+                for (int nb = 0; nb < NBT; ++nb) {
+                    f32x4 d = {0.f, 0.f, 0.f, 0.f};
+                    for (int kc = 0; kc < KCH; ++kc) {
+                        const i32x4 xv = __builtin_amdgcn_raw_buffer_load_b128(in_rs, base + (uint32_t)kc * 64u, 0, 0);
+                        const i32x4 wv = wsrc[((int64_t)(k * KCH + kc) * NB + nb) * 64 + lane];
+                        d = mfma16x16x32<DT>(__builtin_bit_cast(uint4, wv), __builtin_bit_cast(uint4, xv), d);
+                    }
+                    if (have) sum[nb] += d;
+                }
+            }
+#pragma unroll
+            for (int nb = 0; nb < NBT; ++nb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (odd) acc[b][nb][e] = sum[nb][e];
+        }
+    }
+
     // epilogue: act(scale * acc + shift), 4 channels (8 bytes) per store
     const int c0 = ct * NBT * 16 + 4 * g;
     float sc[NBT][4], sh[NBT][4];
@@ -274,80 +311,86 @@ bool union_supported(int K3, int Cin, int Cout, int dt) {
 // 128-row tiles (32 us; 64-row tiles of half the channels 36, the former tile 38).
 // A device-side count (the block's voxels, of a capacity of all its points) is taken as 3/4 of the
 // capacity, about what a LiDAR sweep has.
-template <int KCH, int NB, int CLS>
+template <int K3, int KCH, int NB, int CLS>
 static double union_cost(int64_t rows) {
-    using T = UnionTile<KCH, NB, CLS>;
+    using T = UnionTile<K3, KCH, NB, CLS>;
     if constexpr (!T::valid) {
         return 1e30;
     } else {
         const int64_t wgs = (rows + T::R - 1) / T::R * (NB / T::NBT), slots = 256 * T::per_cu;
         // two workgroups on a CU share its pipes: half a round each beyond the fixed part
-        const double fixed = 4.0 + 0.4 * T::FR, work = T::R / 16 * (0.1 + 0.28 * KCH + 0.018 * T::FR);
+        const double part = K3 / 27.0;  // a 2x2x2 map has 8 of the 27 steps
+        const double fixed = 4.0 + part * 0.4 * T::FR, work = part * T::R / 16 * (0.1 + 0.28 * KCH + 0.018 * T::FR);
         const double full = fixed + work * T::per_cu, rounds = (double)(wgs / slots);
         const int64_t rest = wgs % slots;
         return rounds * full + (rest == 0 ? 0.0 : rest <= 256 ? fixed + work : full);
     }
 }
 
-template <int DT, int KCH, int NB, int CLS>
+template <int DT, int K3, int KCH, int NB, int CLS>
 static void launch_union_tile(hipStream_t s, const ConvPlan& p, const void* in, int64_t in_rows, const void* wpack,
                               const float* scale, const float* shift, int relu, void* out) {
-    using T = UnionTile<KCH, NB, CLS>;
+    using T = UnionTile<K3, KCH, NB, CLS>;
     if constexpr (T::valid) {
         // a multiple of 8 workgroups: the kernel spreads the live tiles over the 8 XCDs
         const unsigned grid = (unsigned)(((p.m_cap + T::R - 1) / T::R + 7) / 8 * 8 * (NB / T::NBT));
-        k_conv_union<DT, KCH, NB, CLS><<<grid, 64 * T::NW, 0, s>>>(p.nbr, p.m_out_dev, p.m_cap, (const uint16_t*)in,
+        k_conv_union<DT, K3, KCH, NB, CLS><<<grid, 64 * T::NW, 0, s>>>(p.nbr, p.m_out_dev, p.m_cap, (const uint16_t*)in,
                                                                   in_rows, (const uint4*)wpack, scale, shift, relu,
                                                                   (const uint16_t*)p.res, (uint16_t*)out);
     }
 }
 
-template <int DT, int KCH, int NB>
+template <int DT, int K3, int KCH, int NB>
 static void launch_union_c(hipStream_t s, const ConvPlan& p, const void* in, int64_t in_rows, const void* wpack,
                            const float* scale, const float* shift, int relu, void* out) {
     const int64_t rows = p.m_out_dev ? p.m_cap - p.m_cap / 4 : p.m_cap;
-    const double cost[5] = {union_cost<KCH, NB, 0>(rows), union_cost<KCH, NB, 1>(rows), union_cost<KCH, NB, 2>(rows),
-                            union_cost<KCH, NB, 3>(rows), union_cost<KCH, NB, 4>(rows)};
+    const double cost[5] = {union_cost<K3, KCH, NB, 0>(rows), union_cost<K3, KCH, NB, 1>(rows), union_cost<K3, KCH, NB, 2>(rows),
+                            union_cost<K3, KCH, NB, 3>(rows), union_cost<K3, KCH, NB, 4>(rows)};
     int c = 0;
     for (int i = 1; i < 5; ++i)
         if (cost[i] < cost[c]) c = i;
     switch (c) {
-        case 0: launch_union_tile<DT, KCH, NB, 0>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
-        case 1: launch_union_tile<DT, KCH, NB, 1>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
-        case 2: launch_union_tile<DT, KCH, NB, 2>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
-        case 3: launch_union_tile<DT, KCH, NB, 3>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
-        case 4: launch_union_tile<DT, KCH, NB, 4>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 0: launch_union_tile<DT, K3, KCH, NB, 0>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 1: launch_union_tile<DT, K3, KCH, NB, 1>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 2: launch_union_tile<DT, K3, KCH, NB, 2>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 3: launch_union_tile<DT, K3, KCH, NB, 3>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 4: launch_union_tile<DT, K3, KCH, NB, 4>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
     }
 }
 
-template <int DT, int KCH>
+template <int DT, int K3, int KCH>
 static void launch_union_cin(hipStream_t s, const ConvPlan& p, const void* in, int Cout, int64_t in_rows,
                              const void* wpack, const float* scale, const float* shift, int relu, void* out) {
     switch (Cout) {
-        case 32: launch_union_c<DT, KCH, 2>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
-        case 64: launch_union_c<DT, KCH, 4>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
-        case 96: launch_union_c<DT, KCH, 6>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
-        case 128: launch_union_c<DT, KCH, 8>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
-        case 256: launch_union_c<DT, KCH, 16>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 32: launch_union_c<DT, K3, KCH, 2>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 64: launch_union_c<DT, K3, KCH, 4>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 96: launch_union_c<DT, K3, KCH, 6>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 128: launch_union_c<DT, K3, KCH, 8>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 256: launch_union_c<DT, K3, KCH, 16>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
     }
 }
 
-template <int DT>
+template <int DT, int K3>
 static void launch_union(hipStream_t s, const ConvPlan& p, const void* in, int Cin, int Cout, int64_t in_rows,
                          const void* wpack, const float* scale, const float* shift, int relu, void* out) {
     switch (Cin) {
-        case 32: launch_union_cin<DT, 1>(s, p, in, Cout, in_rows, wpack, scale, shift, relu, out); break;
-        case 64: launch_union_cin<DT, 2>(s, p, in, Cout, in_rows, wpack, scale, shift, relu, out); break;
-        case 96: launch_union_cin<DT, 3>(s, p, in, Cout, in_rows, wpack, scale, shift, relu, out); break;
-        case 128: launch_union_cin<DT, 4>(s, p, in, Cout, in_rows, wpack, scale, shift, relu, out); break;
-        case 256: launch_union_cin<DT, 8>(s, p, in, Cout, in_rows, wpack, scale, shift, relu, out); break;
+        case 32: launch_union_cin<DT, K3, 1>(s, p, in, Cout, in_rows, wpack, scale, shift, relu, out); break;
+        case 64: launch_union_cin<DT, K3, 2>(s, p, in, Cout, in_rows, wpack, scale, shift, relu, out); break;
+        case 96: launch_union_cin<DT, K3, 3>(s, p, in, Cout, in_rows, wpack, scale, shift, relu, out); break;
+        case 128: launch_union_cin<DT, K3, 4>(s, p, in, Cout, in_rows, wpack, scale, shift, relu, out); break;
+        case 256: launch_union_cin<DT, K3, 8>(s, p, in, Cout, in_rows, wpack, scale, shift, relu, out); break;
     }
 }
 
 void launch_conv_union(hipStream_t s, const ConvPlan& p, const void* in, int Cin, int64_t in_rows, int Cout,
                        const void* wpack, const float* scale, const float* shift, int relu, void* out, int dt) {
-    if (dt == SPV_BF16) launch_union<SPV_BF16>(s, p, in, Cin, Cout, in_rows, wpack, scale, shift, relu, out);
-    else launch_union<SPV_F16>(s, p, in, Cin, Cout, in_rows, wpack, scale, shift, relu, out);
+    if (p.K3 == 8) {
+        if (dt == SPV_BF16) launch_union<SPV_BF16, 8>(s, p, in, Cin, Cout, in_rows, wpack, scale, shift, relu, out);
+        else launch_union<SPV_F16, 8>(s, p, in, Cin, Cout, in_rows, wpack, scale, shift, relu, out);
+    } else {
+        if (dt == SPV_BF16) launch_union<SPV_BF16, 27>(s, p, in, Cin, Cout, in_rows, wpack, scale, shift, relu, out);
+        else launch_union<SPV_F16, 27>(s, p, in, Cin, Cout, in_rows, wpack, scale, shift, relu, out);
+    }
 }
 
 }  // namespace spv

@@ -98,3 +98,65 @@ def test_conv_rows_tiles(spv, cin, cout, dtype, m):
     # half an ulp of the storage type (twice) and float32 sums of 27 * 48 terms at most
     ulp = {"f32": 2.0 ** -23, "bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype]
     assert bool((d <= ulp * scale + 2.0 ** -18 * scale.max()).all()), float((d / scale.max()).max())
+
+
+def stride2(spv, gen, m):
+    """A random set of m fine voxels, its stride-2 map, the parents and offsets of the voxels."""
+    side = int((3 * m) ** (1 / 3)) + 2
+    cell = torch.randperm(side ** 3, generator=gen, device="cuda")[:m].sort().values
+    coords = torch.stack([torch.zeros_like(cell), cell // side ** 2, cell // side % side, cell % side], 1).int()
+    ws = spv.Workspace.for_ops(max(len(cell), 64), 256)
+    km = spv.spv_kernel_map(ws, coords.contiguous(), K=2, stride=2)
+    mc = int(km.m_out_dev.item())
+    off, pairs = km.off.tolist(), km.pairs[: km.total].long()
+    parent, kof = torch.empty(2, len(cell), dtype=torch.long, device="cuda")
+    for k in range(8):
+        i, j = pairs[off[k]: off[k + 1]].T
+        parent[i], kof[i] = j, k
+    return ws, km, mc, parent, kof
+
+
+# the 2x2x2 conv by output (tiles of 64 to 384 coarse rows) and the upsampling (64 or 128 coarse rows of a
+# workgroup, the output channels in one to eight passes), around the edges of their tiles
+@pytest.mark.parametrize("fine,coarse,dtype", [(32, 64, "bf16"), (96, 96, "f16"), (96, 128, "bf16"), (64, 256, "bf16"),
+                                               (256, 32, "f16"), (256, 256, "bf16")])
+@pytest.mark.parametrize("m", [1, 130, 2049, 30_011, 90_001])
+def test_stride2_tiles(spv, fine, coarse, dtype, m):
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(fine * 1000 + coarse + m)
+    ws, km, mc, parent, kof = stride2(spv, gen, m)
+    m = len(parent)
+    x, W = rand(gen, m, fine, dtype=dt), rand(gen, 8, fine, coarse, dtype=dt, std=(2 * fine) ** -0.5)
+    sc, sh = torch.rand(coarse, generator=gen, device="cuda") + 0.5, rand(gen, coarse)
+    ref = torch.zeros(mc, coarse, dtype=torch.float64, device="cuda")
+    for k in range(8):
+        i = torch.nonzero(kof == k)[:, 0]
+        ref[parent[i]] += x[i].double() @ W[k].double()
+    y = spv.spv_sparse_conv(ws, x, km.off, km.pairs, W, mc, scale=sc, shift=sh)
+    assert spv.spv_status_check(ws) == 0
+    close16(y, ref * sc + sh, dt)
+    # an infinite weight reaches the rows that have its offset and no other
+    Wi = W.clone()
+    Wi[3, 0, 1] = float("inf")
+    yi = spv.spv_sparse_conv(ws, x, km.off, km.pairs, Wi, mc, scale=sc, shift=sh)
+    has = torch.zeros(mc, dtype=torch.bool, device="cuda")
+    has[parent[kof == 3]] = True
+    assert bool((torch.isfinite(yi[:, 1].float()) == ~has).all())
+    close16(yi[~has], (ref * sc + sh)[~has], dt)
+    # a workspace without room for the table of 8: the pairs themselves, as before
+    small = spv.Workspace(ws.nbytes)
+    small.nbytes = 4096 + 8 * (mc // 16 + 2) * 4 + 8 * max(fine, 32) * coarse * 2 + 1024
+    close16(spv.spv_sparse_conv(small, x, km.off, km.pairs, W, mc, scale=sc, shift=sh), ref * sc + sh, dt)
+
+    z, Wt = rand(gen, mc, coarse, dtype=dt), rand(gen, 8, coarse, fine, dtype=dt, std=coarse ** -0.5)
+    su, hu, res = torch.rand(fine, generator=gen, device="cuda") + 0.5, rand(gen, fine), rand(gen, m, fine, dtype=dt)
+    children = spv.spv_map_children(ws, km.off, km.pairs, m, mc)
+    refu = torch.empty(m, fine, dtype=torch.float64, device="cuda")
+    for k in range(8):
+        i = torch.nonzero(kof == k)[:, 0]
+        refu[i] = z[parent[i]].double() @ Wt[k].double()
+    up = spv.spv_sparse_conv_up(ws, z, children, Wt, fine, m, scale=su, shift=hu, relu=True, res=res)
+    close16(up, (refu * su + hu + res.double()).relu(), dt)
+    packed = spv.spv_sparse_conv_up_packed(ws, z, children, spv.spv_pack_weights(Wt), fine, m, scale=su, shift=hu,
+                                           relu=True, res=res)
+    assert torch.equal(packed.view(torch.int16), up.view(torch.int16))
