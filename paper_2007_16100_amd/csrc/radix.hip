@@ -21,7 +21,7 @@
 // the sort cover all 64 bits so that they end up last.
 //
 // Up to kMsMaxBlocks histogram blocks of keys, a bucket sort takes the place of
-// the passes when it can (every item valid, at most 32 significant bits, and no
+// the passes when it can (every item valid, at most 40 significant bits, and no
 // bucket over kMsCap items):
 //   k_rs_hist    also counts the keys of each fine bin (their top 12
 //                significant bits) over all keys;
@@ -195,11 +195,15 @@ __device__ inline uint64_t rs_peers(uint32_t d, bool valid, int nbits = BITS) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Geometry of the bucket sort for a key of st.sort_bits (at most 32) bits: the
-// fine bin of a compacted key is key >> shF (its top 12 bits, or all of them);
-// a bucket spans at most 2^spanlog fine bins (so the key bits below its first
-// bin fit 24), and A buckets share the items out by count, the bins'
-// spans adding at most kMsFine >> spanlog more.
+// Geometry of the bucket sort for a key of st.sort_bits (at most kMsKeyBits)
+// bits: the fine bin of a compacted key is key >> shF (its top 12 bits, or all
+// of them); a bucket spans at most 2^spanlog fine bins, so that the key bits
+// below its first bin fit 24 (28 above 32 bits, 32 above 36: a batch of sweeps
+// has 33 or 34, and its spans would otherwise leave no buckets to share out),
+// and A buckets share the items out by count, the bins' spans adding at most
+// kMsFine >> spanlog more.  Measured on two sweeps (200,003 points, 33 bits):
+// 226 us in the fallback's passes, 20 us as buckets.
+constexpr uint32_t kMsKeyBits = 40;
 struct MsGeom {
     uint32_t shF, spanlog, A;
 };
@@ -207,7 +211,7 @@ __device__ inline MsGeom ms_geom(const SortStats& st) {
     MsGeom g;
     const uint32_t F = st.sort_bits < (uint32_t)kMsFineBits ? st.sort_bits : (uint32_t)kMsFineBits;
     g.shF = st.sort_bits - F;
-    g.spanlog = 24 - g.shF;
+    g.spanlog = (st.sort_bits <= 32 ? 24 : st.sort_bits <= 36 ? 28 : 32) - g.shF;
     g.A = kMsMaxBuckets - 1 - (kMsFine >> (g.spanlog < 31 ? g.spanlog : 31));
     return g;
 }
@@ -272,7 +276,7 @@ __global__ __launch_bounds__(kRhThreads) void k_rs_hist(RadixWs w, const int64_t
             if (i < count) {
                 const uint64_t ck = rs_compact(raw[r], st);
                 if (msd) {
-                    if (st.sort_bits <= 32) atomicAdd(&fh[(uint32_t)(ck >> shF)], 1u);  // LDS
+                    if (st.sort_bits <= kMsKeyBits) atomicAdd(&fh[(uint32_t)(ck >> shF)], 1u);  // LDS
                 } else {
                     for (int p = 0; p < passes; ++p)
                         atomicAdd(&hist[p][(uint32_t)(ck >> (kRsBits * p)) & (kRsBins - 1)], 1u);  // LDS
@@ -316,7 +320,7 @@ __global__ __launch_bounds__(kRhThreads) void k_ms_scatter(RadixWs w, const int6
     static_assert(kRsItems * 64 * NWV == kRhTile, "a wave holds kRsItems rounds of 64 keys");
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const SortStats st = *w.st;
-    if (st.n_invalid != 0 || st.sort_bits > 32) return;
+    if (st.n_invalid != 0 || st.sort_bits > kMsKeyBits) return;
     const MsGeom g = ms_geom(st);
     const int64_t count = rs_count(count_dev, cap);
     const int64_t base = (int64_t)blockIdx.x * kRhTile;
@@ -400,12 +404,13 @@ __global__ __launch_bounds__(kRhThreads) void k_ms_scatter(RadixWs w, const int6
     for (int j = 0; j < BPT; ++j) fbase[t * BPT + j] = e[j];
     __syncthreads();
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    uint32_t ck[kRsItems], fb[kRsItems], rk[kRsItems];
+    uint64_t ck[kRsItems];
+    uint32_t fb[kRsItems], rk[kRsItems];
 #pragma unroll
     for (int r = 0; r < kRsItems; ++r) {
         const bool valid = base + wave * (kRsItems * 64) + r * 64 + lane < count;
-        ck[r] = valid ? (uint32_t)rs_compact(raw[r], st) : 0u;
-        fb[r] = ck[r] >> g.shF;
+        ck[r] = valid ? rs_compact(raw[r], st) : 0ull;
+        fb[r] = (uint32_t)(ck[r] >> g.shF);
         const uint64_t peers = rs_peers<kMsFineBits>(fb[r], valid);
         const uint32_t lr = (uint32_t)__popcll(peers & lt);
         const uint32_t prev = wcnt[wave][fb[r]];
@@ -443,7 +448,7 @@ __global__ __launch_bounds__(kRhThreads) void k_ms_scatter(RadixWs w, const int6
         const int64_t i = base + wave * (kRsItems * 64) + r * 64 + lane;
         if (i < count) {
             const uint32_t pos = fbase[fb[r]] + wcnt[wave][fb[r]] + rk[r];
-            w.kb[pos] = ((uint64_t)(uint32_t)i << 32) | ck[r];
+            w.kb[pos] = ((uint64_t)i << kMsKeyBits) | ck[r];
         }
     }
 }
@@ -720,9 +725,9 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_bucket(RadixWs w, Header* h, 
     if (size == 0) return;
     const MsGeom g = ms_geom(st);
     const uint32_t f0 = ms_firsts(w)[b];
-    const uint32_t kbase = f0 << g.shF;  // the bucket's smallest possible key
-    const uint32_t span = (ms_firsts(w)[b + 1] - f0) << g.shF;  // at most 2^24
-    const int bits = (span > 1 ? 32 - __clz(span - 1) : 0) + 8;  // key below kbase, then the block
+    const uint64_t kbase = (uint64_t)f0 << g.shF;  // the bucket's smallest possible key
+    const uint64_t span = (uint64_t)(ms_firsts(w)[b + 1] - f0) << g.shF;  // at most 2^32
+    const int bits = (span > 1 ? 64 - __clzll(span - 1) : 0) + 8;  // the block, then the key above kbase
     const uint32_t R = (size + kMsThreads - 1) / kMsThreads;
     // this wave's rounds that hold items (rounds past the bucket are skipped)
     const uint32_t first = wave * R * 64;
@@ -732,9 +737,13 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_bucket(RadixWs w, Header* h, 
     for (int r = 0; r < kMsRounds; ++r) {
         const uint32_t e = (wave * R + r) * 64 + lane;
         const uint64_t x = ((uint32_t)r < R && e < size) ? w.kb[start + e] : 0ull;
-        val[r] = (uint32_t)(x >> 32);
-        key[r] = (((uint32_t)x - kbase) << 8) | (val[r] >> 10);
+        val[r] = (uint32_t)(x >> kMsKeyBits);
+        key[r] = (uint32_t)((x & ((1ull << kMsKeyBits) - 1)) - kbase);
     }
+    // digit p of the sort: the item's block, then the key from its low bits up
+    const auto digit = [&](int r, int p) -> uint32_t {
+        return (p == 0 ? val[r] >> 10 : key[r] >> (kRsBits * (p - 1))) & (kRsBins - 1);
+    };
     __shared__ uint32_t wc[NWV][kRsBins];
     __shared__ int lds[NWV + 1];
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -749,7 +758,7 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_bucket(RadixWs w, Header* h, 
             if ((uint32_t)r >= Rw) continue;
             const uint32_t e = (wave * R + r) * 64 + lane;
             const bool valid = e < size;
-            const uint32_t d = (key[r] >> (kRsBits * p)) & (kRsBins - 1);
+            const uint32_t d = digit(r, p);
             const uint64_t peers = rs_peers(d, valid, nb);
             const uint32_t lr = (uint32_t)__popcll(peers & lt);
             // every lane reads the count before the digit's first lane adds this
@@ -782,7 +791,7 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_bucket(RadixWs w, Header* h, 
             if ((uint32_t)r >= Rw) continue;
             const uint32_t e = (wave * R + r) * 64 + lane;
             if (e < size) {
-                const uint32_t d = (key[r] >> (kRsBits * p)) & (kRsBins - 1);
+                const uint32_t d = digit(r, p);
                 buf[wc[wave][d] + rk[r]] = ((uint64_t)val[r] << 32) | key[r];
             }
         }
@@ -804,7 +813,7 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_bucket(RadixWs w, Header* h, 
         if ((uint32_t)r >= Rw) continue;
         const uint32_t e = (wave * R + r) * 64 + lane;
         if (e < size) {
-            w.ka[start + e] = (uint64_t)(kbase + (key[r] >> 8));
+            w.ka[start + e] = kbase + key[r];
             w.va[start + e] = val[r];
         }
     }

@@ -160,3 +160,26 @@ def test_stride2_tiles(spv, fine, coarse, dtype, m):
     packed = spv.spv_sparse_conv_up_packed(ws, z, children, spv.spv_pack_weights(Wt), fine, m, scale=su, shift=hu,
                                            relu=True, res=res)
     assert torch.equal(packed.view(torch.int16), up.view(torch.int16))
+
+
+# key widths on both sides of where the sort's geometry changes (24, 28 and 32 bits below a bucket's first
+# fine bin) and of where the buckets end and the passes take over (40 bits)
+@pytest.mark.parametrize("bits", [31, 32, 33, 36, 37, 40, 41])
+@pytest.mark.parametrize("n", [300, 70_001, 262_144])
+def test_sort_key_widths(spv, bits, n):
+    gen = torch.Generator(device="cuda").manual_seed(bits * 10 + n)
+    # z in 7 bits, y in 12, the rest shared by x and the batch; clusters make buckets of many sizes
+    bx = min(bits - 19, 14)
+    fields = (bits - 19 - bx, bx, 12, 7)
+    q = torch.stack([torch.randint(0, 2 ** b, (n,), generator=gen, device="cuda") for b in fields], 1)
+    q[n // 2:, 1] = q[n // 2:, 1] % 97 + 5
+    q[0], q[1] = 0, torch.tensor([2 ** (bits - 19 - bx) - 1, 2 ** bx - 1, 4095, 127])
+    xyz = (q[:, 1:] + 0.5).float().contiguous()
+    ws = spv.Workspace.for_ops(n, 16)
+    vox = spv.spv_voxelize(ws, xyz, 1.0, batch=q[:, 0].int().contiguous())
+    keys = ((q[:, 0] << 40) | (q[:, 1] << 20) | (q[:, 2] << 8) | q[:, 3])
+    ref, of, counts = torch.unique(keys, return_inverse=True, return_counts=True)
+    assert vox.m == len(ref) and spv.spv_status_check(ws) == 0
+    c = vox.coords[: vox.m].long()
+    assert torch.equal((c[:, 0] << 40) | (c[:, 1] << 20) | (c[:, 2] << 8) | c[:, 3], ref)
+    assert torch.equal(vox.pt2vox.long(), of) and torch.equal(vox.counts[: vox.m].long(), counts)
