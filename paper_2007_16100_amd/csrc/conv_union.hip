@@ -20,8 +20,11 @@ __device__ __forceinline__ void static_for(F&& f) {
 // ---------------------------------------------------------------------------
 // A workgroup of NW waves computes R = 16 RB NW output rows times NBT blocks of 16 output channels
 // (NB / NBT workgroups share the rows).  A wave owns RB blocks of 16 rows; the accumulators of a
-// block are D = W^T G^T fragments: lane (r16, g) holds output channels nb*16 + 4g .. 4g+3 of row
-// r16, which is also the order in which they are stored.
+// block are D = W^T G^T fragments.  The weight fragments of a pair of channel blocks (2v, 2v + 1) are
+// permuted on their way into LDS (row r16 of block 2v + u holds channel 32 v + 8 (r16 / 4) + 4 u + r16 % 4),
+// so that lane (r16, g) ends with output channels 32 v + 8 g .. + 7 of row r16: a residual load and a store
+// of 16 bytes each, 64 bytes of a row side by side.  An odd NBT keeps the order of the packing (channels
+// nb*16 + 4g .. 4g+3, 8 bytes).
 //
 // What bounds it: at one 88k-voxel sweep 96 -> 96 the parts of a workgroup's life (weight copies, row
 // gathers, fragment reads, products) take 3 / 9 / 11 / 9 of its 48 us and mostly add up, and below
@@ -52,7 +55,8 @@ struct UnionTile {
     static constexpr int NBT = CLS < 3 ? NBL : NBS;
     static constexpr int FR = KCH * NBT;  // 1 KB weight fragments per offset
     static constexpr int RB = CLS == 0 ? 2 : 1;
-    static constexpr int NW = CLS == 0 ? (FR > 32 ? 8 : NB <= 4 && KCH == 1 ? 16 : 12) : CLS == 1 ? (FR > 32 ? 12 : 16) : CLS == 4 ? 4 : 8;
+    static constexpr int NW0 = FR > 32 ? 8 : NB <= 4 && KCH == 1 ? 16 : 12;
+    static constexpr int NW = CLS == 0 ? NW0 : CLS == 1 ? (FR > 32 ? 12 : 16) : CLS == 4 ? 4 : 8;
     static constexpr int R = NW * RB * 16;
     static constexpr int KS = KCH < 4 ? KCH : RB == 2 ? (NW >= 12 ? 2 : 4) : KCH;
     static constexpr int SH = KCH / KS;  // steps per offset
@@ -104,11 +108,20 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW)) void k_conv
     const int nrows = (int)(m - row0 < R ? m - row0 : R);
 
     // weights of offsets k0 .. k0 + nk - 1 (this workgroup's channel blocks) -> buffer buf
+    constexpr bool PAIR = NBT % 2 == 0;
     const i32x4* wsrc = (const i32x4*)wpack + ct * NBT * 64;
+    // byte offset, from the first fragment of the pair, of what this lane copies into fragment 2v + u
+    uint32_t wlane[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int c = 8 * (r16 >> 2) + 4 * u + (r16 & 3);
+        wlane[u] = PAIR ? (uint32_t)((c >> 4) * 64 + (lane & 48) + (c & 15)) * 16u : (uint32_t)lane * 16u;
+    }
     auto load_w = [&](int k0, int nk, int buf) __attribute__((always_inline)) {
         for (int f = wave; f < nk * FR; f += NW) {
             const int kk = f / NBT, nb = f - kk * NBT;  // kk = (k - k0) * KCH + kc
-            lds_dma_x4((uint64_t)(wsrc + ((int64_t)(k0 * KCH + kk) * NB + nb) * 64), (uint32_t)lane * 16u,
+            const int from = PAIR ? nb & ~1 : nb;
+            lds_dma_x4((uint64_t)(wsrc + ((int64_t)(k0 * KCH + kk) * NB + from) * 64), wlane[nb & 1],
                        __builtin_amdgcn_readfirstlane(lds_addr(&wl[buf][f * 64])));
         }
     };
@@ -243,7 +256,7 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW)) void k_conv
                     f32x4 d = {0.f, 0.f, 0.f, 0.f};
                     for (int kc = 0; kc < KCH; ++kc) {
                         const i32x4 xv = __builtin_amdgcn_raw_buffer_load_b128(in_rs, base + (uint32_t)kc * 64u, 0, 0);
-                        const i32x4 wv = wsrc[((int64_t)(k * KCH + kc) * NB + nb) * 64 + lane];
+                        const i32x4 wv = wsrc[((int64_t)(k * KCH + kc) * NB + (PAIR ? nb & ~1 : nb)) * 64 + wlane[nb & 1] / 16];
                         d = mfma16x16x32<DT>(__builtin_bit_cast(uint4, wv), __builtin_bit_cast(uint4, xv), d);
                     }
                     if (have) sum[nb] += d;
@@ -257,39 +270,52 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW)) void k_conv
         }
     }
 
-    // epilogue: act(scale * acc + shift), 4 channels (8 bytes) per store
-    const int c0 = ct * NBT * 16 + 4 * g;
-    float sc[NBT][4], sh[NBT][4];
+    // epilogue: act(scale * acc + shift + res), EC channels per store
+    constexpr int EC = PAIR ? 8 : 4, NE = NBT * 4 / EC;  // channels of a piece, pieces
+    const int c0 = ct * NBT * 16 + EC * g;
 #pragma unroll
-    for (int nb = 0; nb < NBT; ++nb)
+    for (int v = 0; v < NE; ++v) {
+        float sc[EC], sh[EC];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            sc[nb][e] = scale ? scale[c0 + nb * 16 + e] : 1.f;
-            sh[nb][e] = shift ? shift[c0 + nb * 16 + e] : 0.f;
+        for (int e = 0; e < EC; ++e) {
+            sc[e] = scale ? scale[c0 + v * 4 * EC + e] : 1.f;
+            sh[e] = shift ? shift[c0 + v * 4 * EC + e] : 0.f;
         }
 #pragma unroll
-    for (int b = 0; b < RB; ++b) {
-        const int rr = (wave * RB + b) * 16 + r16;
-        if (rr >= nrows) continue;
+        for (int b = 0; b < RB; ++b) {
+            const int rr = (wave * RB + b) * 16 + r16;
+            if (rr >= nrows) continue;
+            const int64_t at = (row0 + rr) * Cout + c0 + v * 4 * EC;
+            uint32_t u[EC / 2], w[EC / 2];
 #pragma unroll
-        for (int nb = 0; nb < NBT; ++nb) {
-            const int64_t at = (row0 + rr) * Cout + c0 + nb * 16;
-            float y[4], rv[4] = {0.f, 0.f, 0.f, 0.f};
+            for (int e = 0; e < EC / 2; ++e) u[e] = 0u;
             if (res) {  // the residual input, same layout as the output
-                const uint2 u = *(const uint2*)(res + at);
-                rv[0] = from16<DT>(u.x & 0xFFFF);
-                rv[1] = from16<DT>(u.x >> 16);
-                rv[2] = from16<DT>(u.y & 0xFFFF);
-                rv[3] = from16<DT>(u.y >> 16);
+                if constexpr (PAIR) {
+                    const uint4 r = *(const uint4*)(res + at);
+                    u[0] = r.x;
+                    u[1] = r.y;
+                    u[2] = r.z;
+                    u[3] = r.w;
+                } else {
+                    const uint2 r = *(const uint2*)(res + at);
+                    u[0] = r.x;
+                    u[1] = r.y;
+                }
             }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                y[e] = acc[b][nb][e] * sc[nb][e] + sh[nb][e] + rv[e];
-                if (relu) y[e] = fmaxf(y[e], 0.f);
+            for (int e = 0; e < EC; e += 2) {
+                float y[2];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int i = e + q;
+                    const float rv = from16<DT>(q ? u[e / 2] >> 16 : u[e / 2] & 0xFFFF);
+                    y[q] = acc[b][v * (EC / 4) + i / 4][i % 4] * sc[i] + sh[i] + rv;
+                    if (relu) y[q] = fmaxf(y[q], 0.f);
+                }
+                w[e / 2] = (uint32_t)to16<DT>(y[0]) | ((uint32_t)to16<DT>(y[1]) << 16);
             }
-            const uint32_t lo = (uint32_t)to16<DT>(y[0]) | ((uint32_t)to16<DT>(y[1]) << 16);
-            const uint32_t hi = (uint32_t)to16<DT>(y[2]) | ((uint32_t)to16<DT>(y[3]) << 16);
-            *(uint2*)(out + at) = make_uint2(lo, hi);
+            if constexpr (PAIR) *(uint4*)(out + at) = make_uint4(w[0], w[1], w[2], w[3]);
+            else *(uint2*)(out + at) = make_uint2(w[0], w[1]);
         }
     }
 }
