@@ -8,14 +8,15 @@
 //   output channels, accumulated in registers.  For each of the 27 offsets it
 //   gathers the 16 rows' neighbours (zeros where a neighbour is absent) and
 //   multiplies them by W[k] on v_mfma_f32_16x16x32_{bf16,f16}; blocks whose
-//   rows have no neighbour at that offset skip it.  The weights of a phase of
-//   offsets are staged per workgroup in LDS (global->LDS copies), and each
+//   rows have no neighbour at that offset skip it.  The weights of a group of
+//   offsets are copied to LDS while the group before is multiplied, and each
 //   wave's gathers for the next offset are in flight while the current one is
 //   multiplied.  The cost is MFMA work on absent neighbours: on a LiDAR sweep
 //   the 16-row unions of present offsets are ~3x the pairs.  Widths C_in,
-//   C_out in {32, 64, 96, 128, 256}; submanifold and strided 3x3x3 maps.
+//   C_out in {32, 64, 96, 128, 256}; submanifold and strided 3x3x3 maps,
+//   and 2x2x2 stride-2 maps by output on a table of 8.
 //
-// * k_conv_tile (K = 2 maps, transposed maps -- where a 16-row union would be
+// * k_conv_tile (transposed maps -- where a 16-row union would be
 //   mostly empty -- and the other widths): output rows in tiles of T with an
 //   LDS fp32 accumulator; the pairs of each (tile, offset) are a contiguous
 //   slice of the kernel map, multiplied 16 at a time and added into their
