@@ -45,6 +45,11 @@ __device__ __forceinline__ void static_for(F&& f) {
 // blocks with no neighbour at k skip their products.  The copies the compiler does not see are
 // issued after the group's first rows have arrived and waited for by count before the barrier: the
 // loads issued after them are the rows of the steps ahead.
+//
+// On a table of 8 each offset's products are summed by themselves and then added to the rows that have the
+// offset, as the pairs' kernel sums them (the same bits): chained through one accumulator as on 27 offsets,
+// the outputs differed with the kernel that a workspace's size selects, and the rows that an infinite weight
+// reached had to be summed again after the loop, which held up to 160 more registers than the loop itself.
 // shape of a workgroup's tile; valid when it fits in LDS and in the registers of a wave
 template <int K3, int KCH, int NB, int CLS>
 struct UnionTile {
@@ -55,10 +60,11 @@ struct UnionTile {
     static constexpr int NBT = CLS < 3 ? NBL : NBS;
     static constexpr int FR = KCH * NBT;  // 1 KB weight fragments per offset
     static constexpr int RB = CLS == 0 ? 2 : 1;
-    static constexpr int NW0 = FR > 32 ? 8 : NB <= 4 && KCH == 1 ? 16 : 12;
+    static constexpr int NW0 = FR > 32 || (K3 == 8 && FR >= 24) ? 8 : NB <= 4 && KCH == 1 ? 16 : 12;
     static constexpr int NW = CLS == 0 ? NW0 : CLS == 1 ? (FR > 32 ? 12 : 16) : CLS == 4 ? 4 : 8;
     static constexpr int R = NW * RB * 16;
-    static constexpr int KS = KCH < 4 ? KCH : RB == 2 ? (NW >= 12 ? 2 : 4) : KCH;
+    // (a table of 8 sums an offset's products apart, so its steps are whole offsets)
+    static constexpr int KS = KCH < 4 || K3 == 8 ? KCH : RB == 2 ? (NW >= 12 ? 2 : 4) : KCH;
     static constexpr int SH = KCH / KS;  // steps per offset
     static constexpr int RA = SH == 4 ? 3 : K3 == 27 && CLS == 0 && KCH == 3 && NBT <= 6 ? 2 : 1;
     static constexpr int IX = R * K3 + 32;  // table entries (and the few the last steps read past them)
@@ -141,16 +147,20 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW)) void k_conv
     const __amdgpu_buffer_rsrc_t in_rs = make_rsrc(in, (uint32_t)(in_rows * (int64_t)row_bytes));
     const uint32_t in_rows32 = (uint32_t)in_rows;
     const int32_t* ixw = ix + (wave * RB * 16 + r16) * K3;
-    // offsets present in each block (union over its 16 rows), wave-uniform
-    uint32_t umask[RB];
+    // offsets that this lane's row of each block has, and those of the block (union over its 16 rows,
+    // wave-uniform)
+    uint32_t rmask[RB], umask[RB];
 #pragma unroll
     for (int b = 0; b < RB; ++b) {
         uint32_t bits = 0;
 #pragma unroll
         for (int k = 0; k < K3; k += 4)
             if (k + g < K3) bits |= (ixw[b * 16 * K3 + k + g] > 0 ? 1u : 0u) << (k + g);
+        bits |= __shfl_xor(bits, 16, 64);
+        bits |= __shfl_xor(bits, 32, 64);
+        rmask[b] = bits;
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) bits |= __shfl_xor(bits, d, 64);
+        for (int d = 1; d < 16; d <<= 1) bits |= __shfl_xor(bits, d, 64);
         umask[b] = __builtin_amdgcn_readfirstlane(bits);
     }
     // gathered rows of (offset k, slab h): 16-byte chunks g + 4 (h KS + kc) of row i (stored as i + 1)
@@ -198,19 +208,51 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW)) void k_conv
                 for (int b = 0; b < RB; ++b) present |= ((umask[b] >> k) & 1u) << b;
                 if (present) {
                     const i32x4* wk = wbuf + (kp * FR + h * KS * NBT) * 64;
+                    if constexpr (K3 == 8) {
+                        // an offset's products are summed by themselves and added to the rows that have it: half
+                        // of a block's rows lack an offset that the block has, and an infinite weight must not
+                        // reach them (the sums are those of the pairs' kernel, bit for bit)
+                        constexpr int NQ = NBT % 4 == 0 ? 4 : NBT % 3 == 0 ? 3 : 2;
 #pragma unroll
-                    for (int kc = 0; kc < KS; ++kc) {
-                        i32x4 wf[NBT];
+                        for (int q = 0; q < NBT; q += NQ) {
+                            f32x4 d[RB][NQ];
 #pragma unroll
-                        for (int nb = 0; nb < NBT; ++nb) wf[nb] = wk[(kc * NBT + nb) * 64];
+                            for (int b = 0; b < RB; ++b)
 #pragma unroll
-                        for (int b = 0; b < RB; ++b) {
-                            if (RB == 1 || ((present >> b) & 1u)) {
+                                for (int nb = 0; nb < NQ; ++nb) d[b][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                                for (int nb = 0; nb < NBT; ++nb)
-                                    acc[b][nb] = mfma16x16x32<DT>(
-                                        __builtin_bit_cast(uint4, wf[nb]),
-                                        __builtin_bit_cast(uint4, rs[(R0 + j) % (RA + 1)][b][kc]), acc[b][nb]);
+                            for (int kc = 0; kc < KS; ++kc)
+#pragma unroll
+                                for (int nb = 0; nb < NQ; ++nb) {
+                                    const i32x4 wf = wk[(kc * NBT + q + nb) * 64];
+#pragma unroll
+                                    for (int b = 0; b < RB; ++b)
+                                        d[b][nb] = mfma16x16x32<DT>(
+                                            __builtin_bit_cast(uint4, wf),
+                                            __builtin_bit_cast(uint4, rs[(R0 + j) % (RA + 1)][b][kc]), d[b][nb]);
+                                }
+#pragma unroll
+                            for (int b = 0; b < RB; ++b)
+                                if ((rmask[b] >> k) & 1u) {
+#pragma unroll
+                                    for (int nb = 0; nb < NQ; ++nb) acc[b][q + nb] += d[b][nb];
+                                }
+                        }
+                    } else {
+#pragma unroll
+                        for (int kc = 0; kc < KS; ++kc) {
+                            i32x4 wf[NBT];
+#pragma unroll
+                            for (int nb = 0; nb < NBT; ++nb) wf[nb] = wk[(kc * NBT + nb) * 64];
+#pragma unroll
+                            for (int b = 0; b < RB; ++b) {
+                                if (RB == 1 || ((present >> b) & 1u)) {
+#pragma unroll
+                                    for (int nb = 0; nb < NBT; ++nb)
+                                        acc[b][nb] = mfma16x16x32<DT>(
+                                            __builtin_bit_cast(uint4, wf[nb]),
+                                            __builtin_bit_cast(uint4, rs[(R0 + j) % (RA + 1)][b][kc]), acc[b][nb]);
+                                }
                             }
                         }
                     }
@@ -231,44 +273,6 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW)) void k_conv
             constexpr int uu = decltype(u)::value;
             if (U == 1 || gt + uu < NG) group(gt + uu, std::integral_constant<int, uu * GS % (RA + 1)>{});
         });
-
-    if constexpr (K3 == 8) {
-        // Rows without an offset added zeros times its weights, which is nothing unless a weight is infinite
-        // or NaN: a row that is not finite is summed again over its own offsets only (half of a block's rows
-        // lack an offset that the block has, so this must not spread to them).
-#pragma unroll
-        for (int b = 0; b < RB; ++b) {
-            bool odd = false;
-#pragma unroll
-            for (int nb = 0; nb < NBT; ++nb)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) odd = odd || !(fabsf(acc[b][nb][e]) <= 3.402823466e38f);
-            if (!__ballot(odd)) continue;
-            f32x4 sum[NBT];
-#pragma unroll
-            for (int nb = 0; nb < NBT; ++nb) sum[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-            for (int k = 0; k < K3; ++k) {
-                const uint32_t i = (uint32_t)(ixw[b * 16 * K3 + k] - 1);
-                const bool have = i < in_rows32;
-                const uint32_t base = have ? i * row_bytes + (uint32_t)g * 16u : kOutOfRange;
-#pragma unroll
-                for (int nb = 0; nb < NBT; ++nb) {
-                    f32x4 d = {0.f, 0.f, 0.f, 0.f};
-                    for (int kc = 0; kc < KCH; ++kc) {
-                        const i32x4 xv = __builtin_amdgcn_raw_buffer_load_b128(in_rs, base + (uint32_t)kc * 64u, 0, 0);
-                        const i32x4 wv = wsrc[((int64_t)(k * KCH + kc) * NB + (PAIR ? nb & ~1 : nb)) * 64 + wlane[nb & 1] / 16];
-                        d = mfma16x16x32<DT>(__builtin_bit_cast(uint4, wv), __builtin_bit_cast(uint4, xv), d);
-                    }
-                    if (have) sum[nb] += d;
-                }
-            }
-#pragma unroll
-            for (int nb = 0; nb < NBT; ++nb)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (odd) acc[b][nb][e] = sum[nb][e];
-        }
-    }
 
     // epilogue: act(scale * acc + shift + res), EC channels per store
     constexpr int EC = PAIR ? 8 : 4, NE = NBT * 4 / EC;  // channels of a piece, pieces

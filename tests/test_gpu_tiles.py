@@ -162,6 +162,31 @@ def test_stride2_tiles(spv, fine, coarse, dtype, m):
     assert torch.equal(packed.view(torch.int16), up.view(torch.int16))
 
 
+def pairs_workspace(mc, cin, cout):
+    """A workspace with room for the pairs' kernel of a 2x2x2 map and none for its table of 8: the status
+    header, the tile bounds of each offset and the packed weights, each at a multiple of 256 bytes."""
+    from paper_2007_16100_amd import spv
+    return spv.Workspace(256 + (8 * (-(-mc // 16) + 1) * 4 + 255) // 256 * 256 + 8 * cin * cout * 2)
+
+
+# the 2x2x2 conv by output sums each offset's products by themselves, on the table of 8 and on the pairs: the
+# same bits whichever of the two a workspace has room for, infinite weights and sums among them
+@pytest.mark.parametrize("cin,cout,dtype", [(32, 32, "bf16"), (64, 96, "f16"), (96, 128, "bf16"), (128, 256, "f16"),
+                                            (256, 96, "bf16"), (256, 256, "f16")])
+@pytest.mark.parametrize("m", [1, 130, 5003, 30_011, 120_001])
+def test_down_same_bits_on_table_and_pairs(spv, cin, cout, dtype, m):
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(cin * 1000 + cout + m)
+    ws, km, mc, parent, kof = stride2(spv, gen, m)
+    x, W = rand(gen, len(parent), cin, dtype=dt), rand(gen, 8, cin, cout, dtype=dt, std=(2 * cin) ** -0.5)
+    W[5, 0, 3] = float("inf")
+    sc, sh = torch.rand(cout, generator=gen, device="cuda") + 0.5, rand(gen, cout)
+    small = pairs_workspace(mc, cin, cout)
+    table, pairs = (spv.spv_sparse_conv(w, x, km.off, km.pairs, W, mc, scale=sc, shift=sh) for w in (ws, small))
+    assert spv.spv_status_check(ws) == 0 and spv.spv_status_check(small) == 0
+    assert torch.equal(table.view(torch.int16), pairs.view(torch.int16))
+
+
 # key widths on both sides of where the sort's geometry changes (24, 28 and 32 bits below a bucket's first
 # fine bin) and of where the buckets end and the passes take over (40 bits)
 @pytest.mark.parametrize("bits", [31, 32, 33, 36, 37, 40, 41])
