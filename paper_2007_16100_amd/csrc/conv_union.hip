@@ -77,12 +77,23 @@ struct UnionTile {
         return RA == 1 && n == 1 ? 1 : n > most ? most / UNIT * UNIT : n / UNIT * UNIT;
     }
     static constexpr int PH = CLS >= 2 && fit(80) >= 2 ? fit(80) : fit(160);
-    static constexpr bool valid = PH >= 1 && !(CLS == 1 && FR > 48) && !(CLS == 3 && NBS == NBL) && KCH * NBT <= 64;
-    static constexpr int per_cu = (IX * 4 + 2 * PH * FR * 1024) * 2 <= 160 * 1024 ? 2 : 1;
+    static constexpr bool valid = PH >= 1 && !(CLS == 1 && FR > 48) && !(CLS == 3 && NBS == NBL);
+    // channel blocks whose products of an offset are summed at a time, on a table of 8
+    static constexpr int NQ = NBT % 4 == 0 ? 4 : NBT % 3 == 0 ? 3 : 2;
+    // Workgroups that share a CU, by LDS and, on a table of 8, whose small tiles leave room for up to four, by
+    // the registers of a wave: accumulators, the offset's sums, two steps of rows and about 14 more per block
+    // (as many as the compiler takes, or up to 20 more).  The launch bounds hold it to them.  On 27 offsets two fit by LDS only where
+    // 8 waves or fewer do, at under 128 registers.
+    static constexpr int lds_cu = 160 * 1024 / (IX * 4 + 2 * PH * FR * 1024);
+    static constexpr int regs = (4 * RB * (NBT + NQ) + 8 * RB * KCH + 14 * RB + 7) / 8 * 8;
+    static constexpr int reg_cu = 512 / regs * 4 / NW;
+    static constexpr int fit_cu = K3 == 27 ? (lds_cu < 2 ? lds_cu : 2) : lds_cu < reg_cu ? lds_cu : reg_cu;
+    static constexpr int per_cu = fit_cu < 1 ? 1 : fit_cu > 4 ? 4 : fit_cu;
+    static constexpr int waves_eu = K3 == 8 ? per_cu * NW / 4 : 1;
 };
 
 template <int DT, int K3, int KCH, int NB, int CLS>
-__global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW)) void k_conv_union(
+__global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW), (UnionTile<K3, KCH, NB, CLS>::waves_eu)) void k_conv_union(
     const int32_t* __restrict__ nbr, const int64_t* __restrict__ m_out_dev, int64_t m_cap,
     const uint16_t* __restrict__ in, int64_t in_rows, const uint4* __restrict__ wpack,
     const float* __restrict__ scale, const float* __restrict__ shift, int relu, const uint16_t* __restrict__ res,
@@ -212,7 +223,7 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW)) void k_conv
                         // an offset's products are summed by themselves and added to the rows that have it: half
                         // of a block's rows lack an offset that the block has, and an infinite weight must not
                         // reach them (the sums are those of the pairs' kernel, bit for bit)
-                        constexpr int NQ = NBT % 4 == 0 ? 4 : NBT % 3 == 0 ? 3 : 2;
+                        constexpr int NQ = T::NQ;
 #pragma unroll
                         for (int q = 0; q < NBT; q += NQ) {
                             f32x4 d[RB][NQ];
@@ -335,10 +346,14 @@ bool union_supported(int K3, int Cin, int Cout, int dt) {
 
 // Which tile: whole rounds of workgroups over the 256 CUs times what one round takes.  A round of
 // workgroups of B blocks of 16 rows and FR weight fragments per offset measured about
-// 4 + 0.4 FR + B (0.1 + 0.28 KCH + 0.018 FR) us (96 -> 96: 21 us at 8 blocks, 31 at 16, 43 at 24; 32 -> 32:
-// 8 at 8, 15 at 32; 256 -> 256 in slices of 128 channels: 88 at 16, of 64: 60 at 16, of 32: 30 at 8), so a small tile wins while it still fits one round
-// and a large one when rounds are many.  The model only ranks: at 128 -> 128 on 18,631 rows it takes
-// 128-row tiles (32 us; 64-row tiles of half the channels 36, the former tile 38).
+// 4 + 0.4 FR + B (0.1 + 0.28 KCH + 0.018 FR) us on 27 offsets (96 -> 96: 21 us at 8 blocks, 31 at 16, 43 at 24;
+// 32 -> 32: 8 at 8, 15 at 32; 256 -> 256 in slices of 128 channels: 88 at 16, of 64: 60 at 16, 30 at 8) and
+// 1.5 + 0.13 FR + B (0.08 + 0.04 KCH + 0.016 FR) us on 8, beside the plan; so a small tile wins while it still
+// fits one round and a large one when rounds are many.  The model only ranks.  On 8 offsets, every tile of the
+// 25 width pairs timed at 19 sets of 354 to 188,994 coarse rows: the tile ranked first takes 1.1% longer than
+// the fastest on average (27 offsets' constants, scaled, and two workgroups wherever the LDS has room: 1.9%);
+// 64 -> 128 with its plan takes 26 us on 35,193 rows in 384-row tiles, 22 in 256 or 128 rows and 32 on the
+// pairs, and on 69,827 rows 31, 37, 34 and 51.
 // A device-side count (the block's voxels, of a capacity of all its points) is taken as 3/4 of the
 // capacity, about what a LiDAR sweep has.
 template <int K3, int KCH, int NB, int CLS>
@@ -348,12 +363,11 @@ static double union_cost(int64_t rows) {
         return 1e30;
     } else {
         const int64_t wgs = (rows + T::R - 1) / T::R * (NB / T::NBT), slots = 256 * T::per_cu;
-        // two workgroups on a CU share its pipes: half a round each beyond the fixed part
-        const double part = K3 / 27.0;  // a 2x2x2 map has 8 of the 27 steps
-        const double fixed = 4.0 + part * 0.4 * T::FR, work = part * T::R / 16 * (0.1 + 0.28 * KCH + 0.018 * T::FR);
-        const double full = fixed + work * T::per_cu, rounds = (double)(wgs / slots);
-        const int64_t rest = wgs % slots;
-        return rounds * full + (rest == 0 ? 0.0 : rest <= 256 ? fixed + work : full);
+        // workgroups on one CU share its pipes: only the fixed parts overlap
+        const double fixed = K3 == 8 ? 1.5 + 0.13 * T::FR : 4.0 + 0.4 * T::FR;
+        const double work = T::R / 16 * (K3 == 8 ? 0.08 + 0.04 * KCH + 0.016 * T::FR : 0.1 + 0.28 * KCH + 0.018 * T::FR);
+        const int64_t rest = wgs % slots, deep = (rest + 255) / 256;  // of the last round, workgroups on the fullest CU
+        return (double)(wgs / slots) * (fixed + work * T::per_cu) + (rest == 0 ? 0.0 : fixed + work * (double)deep);
     }
 }
 
