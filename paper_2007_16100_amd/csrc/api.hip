@@ -246,8 +246,9 @@ int32_t spv_conv_kernel(int32_t K3, int32_t Cin, int32_t Cout, spv_dtype dt, int
     if (!(K3 == 27 || K3 == 8) || Cin <= 0 || Cout <= 0 || !valid_dt(dt) || in_rows < 0 || m_out_cap < 0 ||
         pair_cap < 0)
         return -1;
-    return conv_kernel_choice(K3, Cin, Cout, dt, m_out_cap > 0 ? m_out_cap : 1, in_rows, pair_cap,
-                              transposed && in_rows != m_out_cap);
+    const int kernel = conv_kernel_choice(K3, Cin, Cout, dt, m_out_cap > 0 ? m_out_cap : 1, in_rows, pair_cap,
+                                          conv_sparse_transposed(K3, transposed, in_rows, m_out_cap));
+    return kernel == kConvTable8 ? kConvTile : kernel;
 }
 
 int32_t spv_block_conv_kernel(int64_t n, int32_t C, spv_dtype dt) {
@@ -371,12 +372,7 @@ static spv_status sparse_conv_call(void* stream, void* ws, size_t ws_bytes, cons
     if ((in_rows > 0 && !in) || (m_out_cap > 0 && !out) || (pair_cap > 0 && !pairs)) return SPV_ERR_INVALID_ARG;
     if (!aligned16(in) || !aligned16(out) || !aligned16(W) || !aligned16(res) || (res && res == out))
         return SPV_ERR_INVALID_ARG;
-    // A transposed stride-2 map gives an output few of the 27 offsets (at most
-    // 8, 2-3 on a sweep), which the neighbour-table kernel would still step
-    // through for every block: the tile kernel, which only visits pairs, takes
-    // it.  A transposed map with as many inputs as outputs (a submanifold map
-    // read backwards, as in the input gradient) is as dense as the forward one.
-    bool sparse_tr = transposed && in_rows != m_out_cap;
+    bool sparse_tr = conv_sparse_transposed(K3, transposed, in_rows, m_out_cap);
     ConvLayout L;
     if (need(layout_conv(nullptr, 0, m_out_cap, K3, Cin, Cout, dt, L, in_rows, sparse_tr), ws_bytes)) {
         // a workspace without room for a 2x2x2 map's table: the pairs themselves (the tile kernel)

@@ -45,12 +45,8 @@ void plan_conv_ws(Arena& a, ConvPlan& p, int64_t m_out_cap, int K3, int Cin, int
     p.K3 = K3;
     // decided once here: launch_conv_plan builds what this kernel reads
     // (neighbour table or tile bounds) and launch_conv_run runs it
-    p.use_union = conv_kernel_choice(K3, Cin, Cout, dt, p.m_cap, in_rows, 0, sparse_transposed) == kConvUnion ? 1 : 0;
-    // a 2x2x2 map by output: the neighbour-table kernel on a table of 8 (64 -> 128 onto 50k voxels of a
-    // sweep: 65 us on the tile kernel's pairs)
-    if (K3 == 8 && !sparse_transposed && union_supported(27, Cin, Cout, dt) && p.m_cap * 32 <= (int64_t)0xFFFFE000 &&
-        conv_fits_buffers(in_rows, Cin, 0))
-        p.use_union = 1;
+    const int kernel = conv_kernel_choice(K3, Cin, Cout, dt, p.m_cap, in_rows, 0, sparse_transposed);
+    p.use_union = kernel == kConvUnion || kernel == kConvTable8 ? 1 : 0;
     p.tile_rows = conv_tile_rows(Cin, Cout, dt, p.m_cap);
     p.ntile_cap = (p.m_cap + p.tile_rows - 1) / p.tile_rows;
     p.bnd = a.take<int32_t>((size_t)K3 * ((p.m_cap + kChunk - 1) / kChunk + 1));
@@ -837,11 +833,13 @@ static bool conv_fits_buffers(int64_t in_rows, int Cin, int64_t pair_bound) {
 
 int conv_kernel_choice(int K3, int Cin, int Cout, int dt, int64_t m_out_cap, int64_t in_rows, int64_t pair_bound,
                        bool sparse_transposed) {
+    // a 2x2x2 map by output runs on a table of 8 (64 -> 128 onto 35,193 voxels of a sweep: 32 us on the tile
+    // kernel's pairs, 22 on the table, both with their plan)
     if (!sparse_transposed && union_supported(K3, Cin, Cout, dt) && m_out_cap * K3 * 4 <= (int64_t)0xFFFFE000 &&
         conv_fits_buffers(in_rows, Cin, 0))
-        return kConvUnion;
+        return K3 == 27 ? kConvUnion : kConvTable8;
     if (conv_mfma_supported(Cin, Cout, dt) && conv_fits_buffers(in_rows, Cin, pair_bound)) return kConvTile;
-    return kConvValu;
+    return kConvRows;
 }
 
 void launch_conv_run(hipStream_t s, const ConvPlan& p, const void* in, int Cin, int64_t in_rows, const int32_t* pairs,

@@ -339,7 +339,7 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW), (UnionTile<
 // blocks and networks built here, square layers and the channel changes
 // between stages); other shapes use the tile kernel
 bool union_supported(int K3, int Cin, int Cout, int dt) {
-    if (K3 != 27 || dt == SPV_F32) return false;
+    if ((K3 != 27 && K3 != 8) || dt == SPV_F32) return false;
     const auto width_ok = [](int c) { return c == 32 || c == 64 || c == 96 || c == 128 || c == 256; };
     return width_ok(Cin) && width_ok(Cout);
 }

@@ -241,12 +241,12 @@ __device__ inline void clear_nbr_upper(int32_t* nbr, int64_t v) {
 }
 
 // --- sparse conv (conv.hip) ----------------------------------------------------
-// Two MFMA kernels share one plan.
-//  * 3x3x3 maps (K3 = 27): output-stationary blocks of 16 rows with register
-//    accumulators; the plan builds a dense neighbour table nbr[j][k] = i + 1
-//    (0 = no pair) from the kernel map.
-//  * other maps (K3 = 8) and wide shapes: output rows in tiles of `tile_rows`
-//    with an LDS accumulator; the plan records, per offset k and tile t, the
+// Two MFMA kernels and a float32 one share one plan.
+//  * 3x3x3 maps (K3 = 27), and 2x2x2 maps by output (K3 = 8): output-stationary
+//    blocks of 16 rows with register accumulators; the plan builds a dense
+//    neighbour table nbr[j][k] = i + 1 (0 = no pair) from the kernel map.
+//  * transposed stride-2 maps and the other widths: output rows in tiles of
+//    `tile_rows` with an LDS accumulator; the plan records, per offset k and tile t, the
 //    first pair of offset k whose output row lies in tile t or later (the
 //    pairs of one offset are sorted by output row, so those of (tile, offset)
 //    form the range [bnd[k][t], bnd[k][t+1])).
@@ -269,11 +269,17 @@ struct ConvPlan {
     int64_t w_ldk = 0;
     int w_ldcol = 0;
 };
-// The kernel a conv runs on, decided on the host from the shape and the sizes
-// (kConvUnion needs every neighbour-table and input offset within 32 bits; a
-// transposed map with fewer inputs than outputs -- sparse_transposed -- goes to
-// the tile kernel, which visits pairs only).
-enum ConvKernel { kConvUnion = 0, kConvTile = 1, kConvValu = 2 };
+// A map read backwards that gives an output few of its offsets: a stride-2 map (an upsampling, or the
+// input gradient of a downsampling) gives it at most 8 of 27, 2-3 on a sweep, and just one of 8.  A 3x3x3 map
+// with as many inputs as outputs is taken for a submanifold map, which is as dense backwards as forwards.
+// A 2x2x2 map never is one, also where its two sides have buffers of one capacity.
+inline bool conv_sparse_transposed(int K3, int transposed, int64_t in_rows, int64_t m_out_cap) {
+    return transposed && (K3 == 8 || in_rows != m_out_cap);
+}
+// The kernel a conv runs on, decided on the host from the shape and the sizes: the neighbour-table kernel
+// on 27 (kConvUnion) or 8 offsets (kConvTable8; both need every table and input offset within 32 bits), the
+// tile kernel, which visits pairs only and so takes sparse transposed maps, or the float32 rows kernel.
+enum ConvKernel { kConvUnion = 0, kConvTile = 1, kConvRows = 2, kConvTable8 = 3 };
 int conv_kernel_choice(int K3, int Cin, int Cout, int dt, int64_t m_out_cap, int64_t in_rows, int64_t pair_bound,
                        bool sparse_transposed);
 // in_rows: rows of the conv's input (the plan's kernel choice depends on it)

@@ -187,6 +187,34 @@ def test_down_same_bits_on_table_and_pairs(spv, cin, cout, dtype, m):
     assert torch.equal(table.view(torch.int16), pairs.view(torch.int16))
 
 
+# a 2x2x2 map read backwards has one offset per output row, also where the coarse side's buffer has the fine
+# side's capacity: it runs on the pairs (the table of 8 would do eight times the products), which shows in the
+# workspace past what the pairs need staying as it was
+@pytest.mark.parametrize("m", [1, 3001])
+@pytest.mark.parametrize("fine,coarse", [(64, 128), (96, 96)])
+def test_transposed_2x2x2_at_equal_capacities(spv, fine, coarse, m):
+    gen = torch.Generator(device="cuda").manual_seed(m + fine)
+    _, km, mc, parent, kof = stride2(spv, gen, m)
+    m = len(parent)
+    z = torch.full((m, coarse), float("nan"), dtype=torch.bfloat16, device="cuda")  # rows past mc: never read
+    z[:mc] = rand(gen, mc, coarse, dtype=torch.bfloat16)
+    Wup = rand(gen, 8, coarse, fine, dtype=torch.bfloat16, std=coarse ** -0.5)
+    Wdown = Wup.transpose(1, 2).contiguous()  # whose input gradient is the same product
+    ref = torch.empty(m, fine, dtype=torch.float64, device="cuda")
+    for k in range(8):
+        i = torch.nonzero(kof == k)[:, 0]
+        ref[i] = z[parent[i]].double() @ Wup[k].double()
+    used = pairs_workspace(m, coarse, fine).nbytes
+    ws = spv.Workspace(used + 64 * m + 4096)
+    start = ws.ptr.value - ws.buf.data_ptr()
+    for call in (lambda: spv.spv_sparse_conv(ws, z, km.off, km.pairs, Wup, m, transposed=True),
+                 lambda: spv.spv_sparse_conv_dgrad(ws, z, km.off, km.pairs, Wdown, m)):
+        ws.buf.fill_(0x5A)
+        close16(call(), ref, torch.bfloat16)
+        assert spv.spv_status_check(ws) == 0
+        assert bool((ws.buf[start + used:] == 0x5A).all())
+
+
 # key widths on both sides of where the sort's geometry changes (24, 28 and 32 bits below a bucket's first
 # fine bin) and of where the buckets end and the passes take over (40 bits)
 @pytest.mark.parametrize("bits", [31, 32, 33, 36, 37, 40, 41])
