@@ -496,11 +496,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
 // Products run on v_mfma_f32_16x16x4_f32 (float32 multiply and add; 16-bit values widen exactly) as
 // D = W^T G^T: of a slab of 16 input channels, lane (r16, g) holds channels 4g .. 4g + 3 of gathered
 // row r16 (one 16-byte load in float32) and of output channel r16, an element of each per
-// instruction.  The loads of the next step are issued before the products of this one.
+// instruction.  The loads of the next step are issued before the products of this one.  Each offset's
+// products are summed by themselves: chained through one accumulator, the sums of a wave's offsets were up to
+// twice as far from 64 bits (256 -> 256 on 6,932 voxels: 5.5e-7 in the 2-norm; 2.9e-7 now, 3.0e-7 in the
+// vector-ALU kernel, which summed this way).
 //
 // It is bound by those loads' latency on few rows and by reading W from L2 once per tile on many.  The
 // vector-ALU kernel it replaced walked each pair's input channels one load at a time: a block of two
-// 16 -> 16 convs on a 2,000-point cloud took 1,100 us, of which they were 925, and takes 101.
+// 16 -> 16 convs on a 2,000-point cloud took 1,100 us, of which they were 925, and takes 101.  The launch
+// bounds keep two waves per SIMD: at 64 rows and 64 channels the compiler takes 312 registers without them and
+// 212 with (96 -> 96 on 35,193 voxels: 333 us; one accumulator chain in 280 registers: 480).
 template <int DT, bool VEC>
 __device__ __forceinline__ f32x4 ld_feat4(const void* p, int64_t row, int C, int c) {
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
@@ -523,7 +528,7 @@ __device__ __forceinline__ f32x4 ld_feat4(const void* p, int64_t row, int C, int
 }
 
 template <int DT, int RB, int NBT, bool VEC>
-__global__ __launch_bounds__(256) void k_conv_rows(ConvPlan p, const void* in, int Cin, int64_t in_rows,
+__global__ __launch_bounds__(256, 2) void k_conv_rows(ConvPlan p, const void* in, int Cin, int64_t in_rows,
                                                    const int32_t* pairs, int64_t pair_bound, int transposed,
                                                    const void* W, const float* scale, const float* shift, int relu,
                                                    void* out, int Cout) {
@@ -593,34 +598,31 @@ __global__ __launch_bounds__(256) void k_conv_rows(ConvPlan p, const void* in, i
                 w[nb][e] = (c + e < Cin && col < Cout) ? ld_feat<DT>(W, k * ldk + (c + e) * ldc + col * ldcol) : 0.f;
         }
     };
-    // A row without this offset holds zeros, which add nothing unless a weight is infinite or NaN: then
-    // the products are formed apart and added to the rows that have it.
-    auto multiply = [&](int kk, const f32x4 (&x)[RB], const f32x4 (&w)[NBT]) __attribute__((always_inline)) {
-        bool odd = false;
+    // An offset's products are summed by themselves and, after its last slab, added to the rows that have it:
+    // a row without it holds zeros, whose product with an infinite weight must not reach it.
+    f32x4 d[RB][NBT];
 #pragma unroll
-        for (int nb = 0; nb < NBT; ++nb)
+    for (int b = 0; b < RB; ++b)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) odd = odd || !(fabsf(w[nb][e]) <= 3.402823466e38f);
-        if (__ballot(odd)) {
-#pragma unroll
-            for (int b = 0; b < RB; ++b)
-#pragma unroll
-                for (int nb = 0; nb < NBT; ++nb) {
-                    f32x4 d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        d = __builtin_amdgcn_mfma_f32_16x16x4f32(w[nb][e], x[b][e], d, 0, 0, 0);
-                    if (ix[kk][b * 16 + r16] > 0) acc[b][nb] += d;
-                }
-            return;
-        }
+        for (int nb = 0; nb < NBT; ++nb) d[b][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int kk, bool last, const f32x4 (&x)[RB], const f32x4 (&w)[NBT]) __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int b = 0; b < RB; ++b)
 #pragma unroll
                 for (int nb = 0; nb < NBT; ++nb)
-                    acc[b][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[nb][e], x[b][e], acc[b][nb], 0, 0, 0);
+                    d[b][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[nb][e], x[b][e], d[b][nb], 0, 0, 0);
+        if (!last) return;
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+            const bool have = ix[kk][b * 16 + r16] > 0;
+#pragma unroll
+            for (int nb = 0; nb < NBT; ++nb) {
+                if (have) acc[b][nb] += d[b][nb];
+                d[b][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
     };
     const int steps = __builtin_popcount(todo) * ns;
     int k = todo ? __builtin_ctz(todo) : 0, sl = 0;
@@ -634,14 +636,16 @@ __global__ __launch_bounds__(256) void k_conv_rows(ConvPlan p, const void* in, i
     if (steps > 0) load(k, sl, x0, w0);
     for (int st = 0; st < steps; st += 2) {
         const int k0 = k;
+        const bool last0 = sl + 1 == ns;
         next();
         const int k1 = k;
+        const bool last1 = sl + 1 == ns;
         if (st + 1 < steps) load(k1, sl, x1, w1);
-        multiply(k0, x0, w0);
+        multiply(k0, last0, x0, w0);
         if (st + 1 < steps) {
             next();
             if (st + 2 < steps) load(k, sl, x0, w0);
-            multiply(k1, x1, w1);
+            multiply(k1, last1, x1, w1);
         }
     }
 #pragma unroll

@@ -100,6 +100,31 @@ def test_conv_rows_tiles(spv, cin, cout, dtype, m):
     assert bool((d <= ulp * scale + 2.0 ** -18 * scale.max()).all()), float((d / scale.max()).max())
 
 
+# Each offset's products are summed by themselves.  With u = 2^-24, a float32 sum of n terms of equal variance is
+# off by u sqrt(n / 6) of its size in the root mean square (the rounding of a step is at most u of a partial sum,
+# a third of its square on average, and the partial sums' squares grow as 1 .. n); so a row of P offsets of cin
+# products is off by u sqrt(cin / 6 + P / 6), and once more by its own rounding.  One chain over a wave's seven
+# offsets would be off by u sqrt(7 cin / 6).
+@pytest.mark.parametrize("cin,cout", [(64, 16), (96, 33), (256, 64)])
+@pytest.mark.parametrize("side", [12, 30])  # 16 and 32 rows of a workgroup
+def test_conv_rows_f32_precision(spv, cin, cout, side):
+    gen = torch.Generator(device="cuda").manual_seed(cin + side)
+    cell = torch.arange(side ** 3, device="cuda")
+    coords = torch.stack([torch.zeros_like(cell), cell // side ** 2, cell // side % side, cell % side], 1).int()
+    m = len(cell)
+    ws = spv.Workspace.for_ops(m, 256)
+    km = spv.spv_kernel_map(ws, coords.contiguous())
+    x, W = rand(gen, m, cin), rand(gen, 27, cin, cout)
+    out = spv.spv_sparse_conv(ws, x, km.off, km.pairs, W, m)
+    off, pairs = km.off.tolist(), km.pairs.long()
+    ref, xd = torch.zeros(m, cout, dtype=torch.float64, device="cuda"), x.double()
+    for k in range(27):
+        i, j = pairs[off[k]: off[k + 1]].T
+        ref[j] += xd[i] @ W[k].double()
+    err = float((out.double() - ref).norm() / ref.norm())
+    assert err <= 2.0 ** -24 * (cin / 6 + 27 / 6 + 1) ** 0.5, err
+
+
 def stride2(spv, gen, m):
     """A random set of m fine voxels, its stride-2 map, the parents and offsets of the voxels."""
     side = int((3 * m) ** (1 / 3)) + 2
