@@ -20,15 +20,18 @@ namespace spv {
 
 constexpr int kLinWaves = 4;
 
-// The kernel of the widths that are a multiple of 32 on both sides.  It moves Cin + Cout (+ Cout of the
-// residual) 16-bit values a row and is bound by how many of those bytes are in flight: a wave's next rows are
+// The kernel of the layers with a residual and widths that are a multiple of 32 on both sides.  It moves
+// Cin + 2 Cout 16-bit values a row and is bound by how many of those bytes are in flight: a wave's next rows are
 // loaded before it multiplies, and the residual of the present ones before the products that it joins.  The
 // fragments of each pair of channel blocks (2v, 2v + 1) are permuted on their way into LDS (row r16 of block
 // 2v + u holds channel 32 v + 8 (r16 / 4) + 4 u + r16 % 4), so that lane (r16, g) ends with channels
-// 32 v + 8 g .. + 7: one 16-byte store, and 64 bytes of a row side by side.  256 -> 128 with a residual over
-// 440k rows: 148 us, against 177 with one row block in flight per wave and 8-byte stores.
+// 32 v + 8 g .. + 7: one 16-byte store, and 64 bytes of a row side by side.  256 -> 128 over 440k rows: 149 us,
+// 178 on k_linear_mfma.  A layer without a residual stays on that one, whose fewer registers let more waves wait
+// for rows (256 -> 128 over 440k rows: 117 us, 139 here; 96 -> 96: 41 and 45).  The launch bounds keep two waves
+// per SIMD where that costs no spills: 128 -> 128 with a residual over 440k rows 80 us in 248 registers, 115 in
+// 264 (k_linear_mfma: 107).
 template <int DT, int KCH, int NB>
-__global__ __launch_bounds__(64 * kLinWaves) void k_linear_rows(
+__global__ __launch_bounds__(64 * kLinWaves, KCH * NB <= 32 && NB <= 8 ? 2 : 1) void k_linear_rows(
     const uint16_t* __restrict__ in, const int64_t* __restrict__ m_dev, int64_t m_cap, const uint4* __restrict__ wpack,
     const float* __restrict__ scale, const float* __restrict__ shift, int relu, const uint16_t* __restrict__ res,
     int res_after, uint16_t* __restrict__ out) {
@@ -63,7 +66,7 @@ __global__ __launch_bounds__(64 * kLinWaves) void k_linear_rows(
         i32x4 rv[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v)
-            rv[v] = res && live ? *(const i32x4*)(res + row * C + 32 * v + 8 * g) : i32x4{0, 0, 0, 0};
+            rv[v] = live ? *(const i32x4*)(res + row * C + 32 * v + 8 * g) : i32x4{0, 0, 0, 0};
         load(blk + stride, nx);
         f32x4 acc[NB];
 #pragma unroll
@@ -234,7 +237,7 @@ static void launch_lin(hipStream_t s, const LinearArgs& a, const void* wpack) {
     if (grid > 1024) grid = 1024;
     if (grid < 1) grid = 1;
     if constexpr (NB % 2 == 0) {
-        if (a.Cout == NB * 16 && a.Cin == KCH * 32) {
+        if (a.res && a.Cout == NB * 16 && a.Cin == KCH * 32) {
             k_linear_rows<DT, KCH, NB><<<(unsigned)grid, 64 * kLinWaves, 0, s>>>(
                 (const uint16_t*)a.in, a.m_dev, a.m_cap, (const uint4*)wpack, a.scale, a.shift, a.relu,
                 (const uint16_t*)a.res, a.res_after, (uint16_t*)a.out);

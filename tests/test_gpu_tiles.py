@@ -240,6 +240,28 @@ def test_transposed_2x2x2_at_equal_capacities(spv, fine, coarse, m):
         assert bool((ws.buf[start + used:] == 0x5A).all())
 
 
+# A wave of the linear kernels takes blocks of 16 rows at a stride of 65,536 rows, two per turn of its loop: row
+# counts with one block per wave, with a second for a few waves, a third, a ragged last one
+@pytest.mark.parametrize("cin,cout,dtype", [(32, 32, "bf16"), (96, 256, "f16"), (128, 128, "bf16"), (256, 96, "bf16"),
+                                            (256, 256, "f16"), (160, 64, "bf16")])
+@pytest.mark.parametrize("m", [65_536, 65_537, 131_090, 200_003])
+@pytest.mark.parametrize("residual", ["none", "before", "after"])
+def test_linear_blocks_per_wave(spv, cin, cout, dtype, m, residual):
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(cin * 1000 + cout + m)
+    live = m - 3 if m % 2 else m
+    x, W = rand(gen, m, cin, dtype=dt), rand(gen, cin, cout, dtype=dt, std=cin ** -0.5)
+    sc, sh = torch.rand(cout, generator=gen, device="cuda") + 0.5, rand(gen, cout)
+    res = None if residual == "none" else rand(gen, m, cout, dtype=dt)
+    out = torch.full((m, cout), 7.0, dtype=dt, device="cuda")
+    spv.spv_linear(spv.Workspace.for_ops(64, 256), x, W, m_dev=torch.tensor([live], device="cuda"), scale=sc, shift=sh,
+                   relu=True, res=res, res_after_act=residual == "after", out=out)
+    ref = (x[:live].double() @ W.double()) * sc + sh
+    r = 0 if res is None else res[:live].double()
+    close16(out[:live], (ref + r).relu() if residual == "before" else ref.relu() + r, dt)
+    assert bool((out[live:] == 7.0).all())  # rows past the count stay
+
+
 # key widths on both sides of where the sort's geometry changes (24, 28 and 32 bits below a bucket's first
 # fine bin) and of where the buckets end and the passes take over (40 bits)
 @pytest.mark.parametrize("bits", [31, 32, 33, 36, 37, 40, 41])
