@@ -1,5 +1,6 @@
-// conv_union.hip -- sparse convolution on a 3x3x3 kernel map (Sec. 3.2 / 3.3)
-// with register accumulators: the neighbour-table kernel described in conv.hip.
+// conv_union.hip -- sparse convolution on a neighbour table of a 3x3x3 map or, by
+// output, of a 2x2x2 one (Sec. 3.2 / 3.3) with register accumulators: the
+// neighbour-table kernel described in conv.hip.
 #include <type_traits>
 
 #include "conv_common.hpp"
@@ -33,9 +34,12 @@ __device__ __forceinline__ void static_for(F&& f) {
 // * the workgroup's rows of the neighbour table go to LDS first, in one coalesced copy: read offset by
 //   offset from memory each 4-byte index cost a lane its own cache line, as much as a gathered row;
 // * the weights of a group of PH offsets are copied global->LDS while the group before is multiplied
-//   (two buffers, one barrier per group, instead of a stop for the copy at each group);
-// * the tile is chosen per call (union_class below): 384 or 512 rows where the rows fill the chip,
-//   down to 64 rows and a slice of the output channels where they do not.  256 -> 256 on 3,161 rows:
+//   (two buffers, one barrier per group, instead of a stop for the copy at each group); where each of two
+//   buffers would hold one offset (48 fragments an offset and more), one buffer of two or three is filled
+//   between two barriers instead: 256 -> 96 on 29,789 rows 48 us, 55 with a barrier at every offset;
+// * the tile is chosen per call (launch_union_c below): 256 to 512 rows where the rows fill the chip, down to
+//   64 rows and a slice of the output channels where they do not, and 192 rows in between at 24 to 32 fragments
+//   an offset (128 -> 128 on 35,193 rows: 44 us, 49 in 256-row tiles).  256 -> 256 on 3,161 rows:
 //   107 -> 31 us, 128 -> 128 on 7,697: 37 -> 17 us, 96 -> 96 on 52,357: 46 -> 33 us, on 88,119: 52 ->
 //   49 us, on 356,951: 171 -> 160 us.
 //
@@ -50,18 +54,19 @@ __device__ __forceinline__ void static_for(F&& f) {
 // offset, as the pairs' kernel sums them (the same bits): chained through one accumulator as on 27 offsets,
 // the outputs differed with the kernel that a workspace's size selects, and the rows that an infinite weight
 // reached had to be summed again after the loop, which held up to 160 more registers than the loop itself.
-// shape of a workgroup's tile; valid when it fits in LDS and in the registers of a wave
+
+// Shape of a workgroup's tile; valid when it fits in LDS and is not another class's tile.
 template <int K3, int KCH, int NB, int CLS>
 struct UnionTile {
     // output-channel blocks of a workgroup: all of them (at most 8) in the classes for many rows, at
     // most half of them in the classes that spread few rows over the chip
     static constexpr int NBL = NB > 8 ? 8 : NB;
     static constexpr int NBS = NB == 2 ? 2 : NB == 4 ? 2 : NB == 6 ? (KCH == 8 ? 3 : 2) : 4;
-    static constexpr int NBT = CLS < 3 ? NBL : NBS;
+    static constexpr int NBT = CLS < 3 || CLS == 5 ? NBL : NBS;
     static constexpr int FR = KCH * NBT;  // 1 KB weight fragments per offset
     static constexpr int RB = CLS == 0 ? 2 : 1;
     static constexpr int NW0 = FR > 32 || (K3 == 8 && FR >= 24) ? 8 : NB <= 4 && KCH == 1 ? 16 : 12;
-    static constexpr int NW = CLS == 0 ? NW0 : CLS == 1 ? (FR > 32 ? 12 : 16) : CLS == 4 ? 4 : 8;
+    static constexpr int NW = CLS == 0 ? NW0 : CLS == 1 ? (FR > 32 ? 12 : 16) : CLS == 4 ? 4 : CLS == 5 ? 12 : 8;
     static constexpr int R = NW * RB * 16;
     // (a table of 8 sums an offset's products apart, so its steps are whole offsets)
     static constexpr int KS = KCH < 4 || K3 == 8 ? KCH : RB == 2 ? (NW >= 12 ? 2 : 4) : KCH;
@@ -76,15 +81,21 @@ struct UnionTile {
         const int most = K3 == 8 ? 4 : 14;
         return RA == 1 && n == 1 ? 1 : n > most ? most / UNIT * UNIT : n / UNIT * UNIT;
     }
-    static constexpr int PH = CLS >= 2 && fit(80) >= 2 ? fit(80) : fit(160);
-    static constexpr bool valid = PH >= 1 && !(CLS == 1 && FR > 48) && !(CLS == 3 && NBS == NBL);
+    static constexpr int PH2 = CLS >= 2 && fit(80) >= 2 ? fit(80) : fit(160);
+    // one buffer where two would hold no more than an offset each
+    static constexpr int PH1 = (160 * 1024 - IX * 4) / (FR * 1024);
+    static constexpr bool TWO = K3 == 8 || PH2 >= 2 || PH1 < 2;
+    static constexpr int PH = TWO ? PH2 : PH1;
+    static constexpr int LDS = IX * 4 + (TWO ? 2 : 1) * PH * FR * 1024;
+    static constexpr bool valid = PH >= 1 && !(CLS == 1 && FR > 48) && !(CLS == 3 && NBS == NBL) &&
+                                  !(CLS == 5 && !(K3 == 27 && FR >= 24 && FR <= 32));
     // channel blocks whose products of an offset are summed at a time, on a table of 8
     static constexpr int NQ = NBT % 4 == 0 ? 4 : NBT % 3 == 0 ? 3 : 2;
     // Workgroups that share a CU, by LDS and, on a table of 8, whose small tiles leave room for up to four, by
     // the registers of a wave: accumulators, the offset's sums, two steps of rows and about 14 more per block
-    // (as many as the compiler takes, or up to 20 more).  The launch bounds hold it to them.  On 27 offsets two fit by LDS only where
-    // 8 waves or fewer do, at under 128 registers.
-    static constexpr int lds_cu = 160 * 1024 / (IX * 4 + 2 * PH * FR * 1024);
+    // (as many as the compiler takes, or up to 20 more).  The launch bounds hold it to them.  On 27 offsets two
+    // fit by LDS only in tiles of at most 8 waves, at under 128 registers each.
+    static constexpr int lds_cu = 160 * 1024 / LDS;
     static constexpr int regs = (4 * RB * (NBT + NQ) + 8 * RB * KCH + 14 * RB + 7) / 8 * 8;
     static constexpr int reg_cu = 512 / regs * 4 / NW;
     static constexpr int fit_cu = K3 == 27 ? (lds_cu < 2 ? lds_cu : 2) : lds_cu < reg_cu ? lds_cu : reg_cu;
@@ -104,7 +115,7 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW), (UnionTile<
     constexpr int Cout = NB * 16, CT = NB / NBT;
     constexpr int U = GS % (RA + 1) == 0 ? 1 : RA + 1;  // groups per turn of the loop: whole turns of the row ring
     static_assert(GS >= RA, "the rows of the steps ahead are issued after the group's weight copies");
-    __shared__ __align__(16) uint4 wl[2][PH * FR * 64];
+    __shared__ __align__(16) uint4 wl[T::TWO ? 2 : 1][PH * FR * 64];
     __shared__ __align__(16) int32_t ix[T::IX];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -135,11 +146,16 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW), (UnionTile<
         wlane[u] = PAIR ? (uint32_t)((c >> 4) * 64 + (lane & 48) + (c & 15)) * 16u : (uint32_t)lane * 16u;
     }
     auto load_w = [&](int k0, int nk, int buf) __attribute__((always_inline)) {
-        for (int f = wave; f < nk * FR; f += NW) {
-            const int kk = f / NBT, nb = f - kk * NBT;  // kk = (k - k0) * KCH + kc
-            const int from = PAIR ? nb & ~1 : nb;
-            lds_dma_x4((uint64_t)(wsrc + ((int64_t)(k0 * KCH + kk) * NB + from) * 64), wlane[nb & 1],
-                       __builtin_amdgcn_readfirstlane(lds_addr(&wl[buf][f * 64])));
+        // (a wave copies both fragments of a pair where nothing overlaps the copy: they share cache lines)
+        constexpr int UF = PAIR && !T::TWO ? 2 : 1;
+        for (int f0 = UF * wave; f0 < nk * FR; f0 += UF * NW) {
+#pragma unroll
+            for (int f = f0; f < f0 + UF; ++f) {
+                const int kk = f / NBT, nb = f - kk * NBT;  // kk = (k - k0) * KCH + kc
+                const int from = PAIR ? nb & ~1 : nb;
+                lds_dma_x4((uint64_t)(wsrc + ((int64_t)(k0 * KCH + kk) * NB + from) * 64), wlane[nb & 1],
+                           __builtin_amdgcn_readfirstlane(lds_addr(&wl[buf][f * 64])));
+            }
         }
     };
     load_w(0, K3 < PH ? K3 : PH, 0);
@@ -199,8 +215,8 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW), (UnionTile<
     auto group = [&](int gi, auto r0) __attribute__((always_inline)) {
         constexpr int R0 = decltype(r0)::value;
         const int k0 = gi * PH;
-        const i32x4* wbuf = (const i32x4*)wl[gi & 1] + lane;
-        if (gi + 1 < NG) {
+        const i32x4* wbuf = (const i32x4*)wl[T::TWO ? gi & 1 : 0] + lane;
+        if (T::TWO && gi + 1 < NG) {
             // the first step's rows are here (the empty statements make the compiler wait for them), so the
             // copies of the next weights delay no row that this step needs
 #pragma unroll
@@ -273,9 +289,17 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW), (UnionTile<
         if (gi + 1 < NG) {
             // of what the wave has issued since the group's weight copies, only the rows of the RA steps
             // ahead may be outstanding: the copies are complete
-            vm_wait<RA * RB * KS>();
+            if constexpr (T::TWO) vm_wait<RA * RB * KS>();
+            lds_wait();
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
+            if constexpr (!T::TWO) {
+                const int k1 = k0 + PH;
+                load_w(k1, K3 - k1 < PH ? K3 - k1 : PH, 0);
+                vm_wait<0>();
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
         }
     };
 #pragma clang loop unroll(disable)
@@ -388,10 +412,11 @@ template <int DT, int K3, int KCH, int NB>
 static void launch_union_c(hipStream_t s, const ConvPlan& p, const void* in, int64_t in_rows, const void* wpack,
                            const float* scale, const float* shift, int relu, void* out) {
     const int64_t rows = p.m_out_dev ? p.m_cap - p.m_cap / 4 : p.m_cap;
-    const double cost[5] = {union_cost<K3, KCH, NB, 0>(rows), union_cost<K3, KCH, NB, 1>(rows), union_cost<K3, KCH, NB, 2>(rows),
-                            union_cost<K3, KCH, NB, 3>(rows), union_cost<K3, KCH, NB, 4>(rows)};
+    const double cost[6] = {union_cost<K3, KCH, NB, 0>(rows), union_cost<K3, KCH, NB, 1>(rows),
+                            union_cost<K3, KCH, NB, 2>(rows), union_cost<K3, KCH, NB, 3>(rows),
+                            union_cost<K3, KCH, NB, 4>(rows), union_cost<K3, KCH, NB, 5>(rows)};
     int c = 0;
-    for (int i = 1; i < 5; ++i)
+    for (int i = 1; i < 6; ++i)
         if (cost[i] < cost[c]) c = i;
     switch (c) {
         case 0: launch_union_tile<DT, K3, KCH, NB, 0>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
@@ -399,6 +424,7 @@ static void launch_union_c(hipStream_t s, const ConvPlan& p, const void* in, int
         case 2: launch_union_tile<DT, K3, KCH, NB, 2>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
         case 3: launch_union_tile<DT, K3, KCH, NB, 3>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
         case 4: launch_union_tile<DT, K3, KCH, NB, 4>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
+        case 5: launch_union_tile<DT, K3, KCH, NB, 5>(s, p, in, in_rows, wpack, scale, shift, relu, out); break;
     }
 }
 

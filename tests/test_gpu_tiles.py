@@ -67,6 +67,31 @@ def test_conv_nbr_tiles(spv, cin, cout, dtype, m):
     assert torch.equal(again[:live].view(torch.int16), out[:live].view(torch.int16))
 
 
+# Row counts among which the rule takes each tile that it ever takes, at every pair of widths (64-row tiles up to
+# 8,232 rows, or 5,530 or 4,100 at 96 or 256 output channels, 128-row tiles of a slice of the channels up to twice
+# that, 128-row tiles of all up to twice that again, 192, 256 and up to 512 rows above): the same bits from all.
+@pytest.mark.parametrize("cin", [32, 64, 96, 128, 256])
+@pytest.mark.parametrize("cout,dtype", [(32, "bf16"), (64, "f16"), (96, "bf16"), (128, "f16"), (256, "bf16")])
+def test_conv_nbr_every_tile(spv, cin, cout, dtype):
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(cin * 1000 + cout)
+    m = 70_001
+    x, W = rand(gen, m, cin, dtype=dt), rand(gen, 27, cin, cout, dtype=dt, std=(27 * cin) ** -0.5)
+    nbr = torch.randint(1, m + 1, (m, 27), generator=gen, device="cuda", dtype=torch.int32)
+    nbr[torch.rand(m, 27, generator=gen, device="cuda") < 0.7] = 0
+    nbr[m // 3: m // 2, 5:20] = 0
+    xd, ref = x.double(), torch.zeros(m, cout, dtype=torch.float64, device="cuda")
+    for k in range(27):
+        j = torch.nonzero(nbr[:, k])[:, 0]
+        ref[j] += xd[(nbr[j, k] - 1).long()] @ W[k].double()
+    ws, P = spv.Workspace.for_ops(m, 256), spv.spv_pack_weights(W)
+    whole = spv.spv_sparse_conv_nbr_packed(ws, x, nbr, P, cout, m)
+    close16(whole, ref, dt)
+    for rows in (3000, 6001, 9003, 12_005, 20_000, 28_009, 40_003, 58_111):
+        part = spv.spv_sparse_conv_nbr_packed(ws, x, nbr, P, cout, rows)
+        assert torch.equal(part.view(torch.int16), whole[:rows].view(torch.int16)), rows
+
+
 # 16, 32 and 64 rows of a workgroup and the capacities at which the rule changes between them; widths
 # that are no multiple of 4 (element loads), of 16, and over one workgroup's 64 output channels
 @pytest.mark.parametrize("cin,cout,dtype", [(16, 16, "f32"), (5, 19, "f32"), (48, 70, "f32"), (6, 9, "bf16"),
@@ -210,6 +235,26 @@ def test_down_same_bits_on_table_and_pairs(spv, cin, cout, dtype, m):
     table, pairs = (spv.spv_sparse_conv(w, x, km.off, km.pairs, W, mc, scale=sc, shift=sh) for w in (ws, small))
     assert spv.spv_status_check(ws) == 0 and spv.spv_status_check(small) == 0
     assert torch.equal(table.view(torch.int16), pairs.view(torch.int16))
+
+
+# the same for the table of 8, whose rule takes its largest tile above 16,486 to 100,078 coarse rows
+@pytest.mark.parametrize("cin", [32, 64, 96, 128, 256])
+@pytest.mark.parametrize("cout,dtype", [(32, "f16"), (64, "bf16"), (96, "f16"), (128, "bf16"), (256, "f16")])
+def test_down_every_tile(spv, cin, cout, dtype):
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(cin * 1000 + cout)
+    ws, km, mc, parent, kof = stride2(spv, gen, 290_000)
+    assert mc > 100_100
+    x, W = rand(gen, len(parent), cin, dtype=dt), rand(gen, 8, cin, cout, dtype=dt, std=(2 * cin) ** -0.5)
+    pairs = spv.spv_sparse_conv(pairs_workspace(mc, cin, cout), x, km.off, km.pairs, W, mc)
+    ref = torch.zeros(mc, cout, dtype=torch.float64, device="cuda")
+    for k in range(8):
+        i = torch.nonzero(kof == k)[:, 0]
+        ref[parent[i]] += x[i].double() @ W[k].double()
+    close16(pairs, ref, dt)
+    for rows in (3000, 6001, 9003, 12_005, 23_000, 29_009, 40_003, 58_111, 70_001, mc):
+        part = spv.spv_sparse_conv(ws, x, km.off, km.pairs, W, rows)
+        assert torch.equal(part.view(torch.int16), pairs[:rows].view(torch.int16)), rows
 
 
 # a 2x2x2 map read backwards has one offset per output row, also where the coarse side's buffer has the fine
