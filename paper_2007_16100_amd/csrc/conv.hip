@@ -538,11 +538,10 @@ __global__ __launch_bounds__(256, 2) void k_conv_rows(ConvPlan p, const void* in
     const int K3 = p.K3, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, g = lane >> 4;
-    const int64_t t = blockIdx.x;
+    const int TP = p.tile_rows;  // rows of a tile of the plan: T, or 2 T (launch_rows)
     const int64_t m = clamp_rows(p.m_out_dev, p.m_cap);
-    const int64_t nt = (m + T - 1) / T;
-    if (t >= nt) return;
-    const int64_t row0 = t * T;
+    const int64_t row0 = (int64_t)blockIdx.x * T, t = row0 / TP;
+    if (row0 >= m) return;
     const int rows = (int)((m - row0) < T ? (m - row0) : T);
     const int col0 = blockIdx.y * CW;
 
@@ -550,14 +549,14 @@ __global__ __launch_bounds__(256, 2) void k_conv_rows(ConvPlan p, const void* in
     __syncthreads();
     const int isel = transposed ? 1 : 0;
     const int64_t bs = p.ntile_cap + 1;
-    for (int e = tid; e < K3 * T; e += 256) {
-        // at most T pairs of an offset have their output row in the tile (a map with more is not a
+    for (int e = tid; e < K3 * TP; e += 256) {
+        // at most TP pairs of an offset have their output row in the tile (a map with more is not a
         // kernel map, which the plan reports); clamped into the pair list
-        const int k = e / T;
+        const int k = e / TP;
         int64_t lo = p.bnd[k * bs + t], hi = p.bnd[k * bs + t + 1];
         lo = lo < 0 ? 0 : (lo > pair_bound ? pair_bound : lo);
         hi = hi < lo ? lo : (hi > pair_bound ? pair_bound : hi);
-        const int64_t pi = lo + e % T;
+        const int64_t pi = lo + e % TP;
         if (pi >= hi) continue;
         const int32_t i = pairs[2 * pi + isel];
         const int64_t o = (int64_t)pairs[2 * pi + 1 - isel] - row0;
@@ -769,7 +768,7 @@ template <int DT, int RB, int NBT>
 static void launch_rows_c(hipStream_t s, const ConvPlan& p, const void* in, int Cin, int64_t in_rows,
                           const int32_t* pairs, int64_t pair_bound, int transposed, const void* W, const float* scale,
                           const float* shift, int relu, void* out, int Cout) {
-    const dim3 grid((unsigned)(p.ntile_cap > 0 ? p.ntile_cap : 1), (unsigned)((Cout + 16 * NBT - 1) / (16 * NBT)));
+    const dim3 grid((unsigned)((p.m_cap + 16 * RB - 1) / (16 * RB)), (unsigned)((Cout + 16 * NBT - 1) / (16 * NBT)));
     if (Cin % 4 == 0)
         k_conv_rows<DT, RB, NBT, true><<<grid, 256, 0, s>>>(p, in, Cin, in_rows, pairs, pair_bound, transposed, W,
                                                             scale, shift, relu, out, Cout);
@@ -784,22 +783,20 @@ static void launch_rows(hipStream_t s, const ConvPlan& p, const void* in, int Ci
                         const int32_t* pairs, int64_t pair_bound, int transposed, const void* W, const float* scale,
                         const float* shift, int relu, void* out, int Cout) {
 #define SPV_ROWS_CASE(T)                                                                                              \
-    case T:                                                                                                           \
-        if (Cout <= 16)                                                                                               \
-            launch_rows_c<DT, T / 16, 1>(s, p, in, Cin, in_rows, pairs, pair_bound, transposed, W, scale, shift, relu, \
-                                         out, Cout);                                                                  \
-        else if (Cout <= 32)                                                                                          \
-            launch_rows_c<DT, T / 16, 2>(s, p, in, Cin, in_rows, pairs, pair_bound, transposed, W, scale, shift, relu, \
-                                         out, Cout);                                                                  \
-        else                                                                                                          \
-            launch_rows_c<DT, T / 16, 4>(s, p, in, Cin, in_rows, pairs, pair_bound, transposed, W, scale, shift, relu, \
-                                         out, Cout);                                                                  \
-        break;
+    if (Cout <= 16)                                                                                                   \
+        launch_rows_c<DT, T / 16, 1>(s, p, in, Cin, in_rows, pairs, pair_bound, transposed, W, scale, shift, relu, out, \
+                                     Cout);                                                                           \
+    else if (Cout <= 32)                                                                                              \
+        launch_rows_c<DT, T / 16, 2>(s, p, in, Cin, in_rows, pairs, pair_bound, transposed, W, scale, shift, relu, out, \
+                                     Cout);                                                                           \
+    else                                                                                                              \
+        launch_rows_c<DT, T / 16, 4>(s, p, in, Cin, in_rows, pairs, pair_bound, transposed, W, scale, shift, relu, out, \
+                                     Cout)
     switch (p.tile_rows) {
-        SPV_ROWS_CASE(16)
-        SPV_ROWS_CASE(32)
-        SPV_ROWS_CASE(64)
-        SPV_ROWS_CASE(128)  // the tile kernel's plan, where the pair list is too long for that kernel
+        case 16: SPV_ROWS_CASE(16); break;
+        case 32: SPV_ROWS_CASE(32); break;
+        // 128: the tile kernel's plan, where its input or pair list is too long for that kernel
+        default: SPV_ROWS_CASE(64); break;
     }
 #undef SPV_ROWS_CASE
 }

@@ -285,6 +285,27 @@ def test_transposed_2x2x2_at_equal_capacities(spv, fine, coarse, m):
         assert bool((ws.buf[start + used:] == 0x5A).all())
 
 
+# 16-bit widths of the tile kernel whose pair list has no 32-bit byte offsets (its capacity counts, not its
+# pairs) run on the rows kernel, over the tile kernel's plan of up to 128 rows
+@pytest.mark.parametrize("cin,cout", [(32, 32), (96, 64)])
+@pytest.mark.parametrize("m", [100, 5003])
+def test_rows_kernel_on_the_tile_kernels_plan(spv, cin, cout, m):
+    gen = torch.Generator(device="cuda").manual_seed(m + cin)
+    ws, km, mc, parent, kof = stride2(spv, gen, m)
+    m = len(parent)
+    pairs = torch.empty((0xFFFFE000 // 8 + 1, 2), dtype=torch.int32, device="cuda")
+    pairs[: km.total] = km.pairs[: km.total]
+    assert spv.spv_conv_kernel(8, cin, cout, torch.bfloat16, mc, m, len(pairs), True) == 2
+    z, W = rand(gen, mc, cin, dtype=torch.bfloat16), rand(gen, 8, cin, cout, dtype=torch.bfloat16, std=cin ** -0.5)
+    ref = torch.empty(m, cout, dtype=torch.float64, device="cuda")
+    for k in range(8):
+        i = torch.nonzero(kof == k)[:, 0]
+        ref[i] = z[parent[i]].double() @ W[k].double()
+    out = spv.spv_sparse_conv(ws, z, km.off, pairs, W, m, transposed=True)
+    assert spv.spv_status_check(ws) == 0
+    close16(out, ref, torch.bfloat16)
+
+
 # A wave of the linear kernels takes blocks of 16 rows at a stride of 65,536 rows, two per turn of its loop: row
 # counts with one block per wave, with a second for a few waves, a third, a ragged last one
 @pytest.mark.parametrize("cin,cout,dtype", [(32, 32, "bf16"), (96, 256, "f16"), (128, 128, "bf16"), (256, 96, "bf16"),
