@@ -1,6 +1,7 @@
 // conv_union.hip -- sparse convolution on a neighbour table of a 3x3x3 map or, by
 // output, of a 2x2x2 one (Sec. 3.2 / 3.3) with register accumulators: the
 // neighbour-table kernel described in conv.hip.
+#include <algorithm>
 #include <type_traits>
 
 #include "conv_common.hpp"
@@ -100,6 +101,8 @@ struct UnionTile {
     static constexpr int reg_cu = 512 / regs * 4 / NW;
     static constexpr int fit_cu = K3 == 27 ? (lds_cu < 2 ? lds_cu : 2) : lds_cu < reg_cu ? lds_cu : reg_cu;
     static constexpr int per_cu = fit_cu < 1 ? 1 : fit_cu > 4 ? 4 : fit_cu;
+    static constexpr bool SPREAD = K3 == 27 && RB == 2;      // spreads few live rows
+    static constexpr int SLOTS = 256 / (NB / NBT);           // row tiles that give every CU one workgroup
     static constexpr int waves_eu = K3 == 8 ? per_cu * NW / 4 : 1;
 };
 
@@ -130,10 +133,23 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW), (UnionTile<
     const int64_t m = clamp_rows(m_out_dev, m_cap);
     const int64_t x = blockIdx.x % 8, seq = blockIdx.x / 8 / CT;
     const int ct = (int)(blockIdx.x / 8 % CT);
-    const int64_t ga = (m + R - 1) / R, xq = ga / 8, xr = ga % 8;
+    // A tile of two blocks a wave was picked for a capacity.  Where the live rows, at one block for each wave, do
+    // not fill the chip once, they are spread: tiles of as few blocks as that takes, a wave each (the other
+    // waves and the second blocks find no rows).  128 -> 128 in buffers of 120,000 rows, 6,000 of them live:
+    // 35 us, 60 in whole tiles, 41 in the one-block tiles that served it before.
+    int RL = R;
+    bool spread = false;
+    if (T::SPREAD && m_out_dev) {
+        const int64_t nb = (m + 16 * T::SLOTS - 1) / (16 * T::SLOTS);
+        spread = nb <= NW;
+        if (spread) RL = nb > 1 ? 16 * (int)nb : 16;
+    }
+    // rows of block b of a wave: wave * wave_rows + b * block_rows ..
+    const int wave_rows = spread ? 16 : 16 * RB, block_rows = spread ? 16 * NW : 16;
+    const int64_t ga = spread ? (uint32_t)(m + RL - 1) / (uint32_t)RL : (m + R - 1) / R, xq = ga / 8, xr = ga % 8;
     if (seq >= xq + (x < xr ? 1 : 0)) return;  // the whole workgroup
-    const int64_t row0 = (x * xq + (x < xr ? x : xr) + seq) * R;
-    const int nrows = (int)(m - row0 < R ? m - row0 : R);
+    const int64_t row0 = (x * xq + (x < xr ? x : xr) + seq) * RL;
+    const int nrows = (int)(m - row0 < RL ? m - row0 : RL);
 
     // weights of offsets k0 .. k0 + nk - 1 (this workgroup's channel blocks) -> buffer buf
     constexpr bool PAIR = NBT % 2 == 0;
@@ -173,7 +189,8 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW), (UnionTile<
     constexpr uint32_t row_bytes = KCH * 64u;
     const __amdgpu_buffer_rsrc_t in_rs = make_rsrc(in, (uint32_t)(in_rows * (int64_t)row_bytes));
     const uint32_t in_rows32 = (uint32_t)in_rows;
-    const int32_t* ixw = ix + (wave * RB * 16 + r16) * K3;
+    const int32_t* ixw = ix + (wave * wave_rows + r16) * K3;
+    const int bstep = block_rows * K3;  // table entries between a wave's blocks
     // offsets that this lane's row of each block has, and those of the block (union over its 16 rows,
     // wave-uniform)
     uint32_t rmask[RB], umask[RB];
@@ -182,7 +199,7 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW), (UnionTile<
         uint32_t bits = 0;
 #pragma unroll
         for (int k = 0; k < K3; k += 4)
-            if (k + g < K3) bits |= (ixw[b * 16 * K3 + k + g] > 0 ? 1u : 0u) << (k + g);
+            if (k + g < K3) bits |= (ixw[b * bstep + k + g] > 0 ? 1u : 0u) << (k + g);
         bits |= __shfl_xor(bits, 16, 64);
         bits |= __shfl_xor(bits, 32, 64);
         rmask[b] = bits;
@@ -194,7 +211,7 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW), (UnionTile<
     auto load_rows = [&](int k, int h, i32x4 (&dst)[RB][KS]) __attribute__((always_inline)) {
 #pragma unroll
         for (int b = 0; b < RB; ++b) {
-            const uint32_t i = (uint32_t)(ixw[b * 16 * K3 + k] - 1);
+            const uint32_t i = (uint32_t)(ixw[b * bstep + k] - 1);
             const uint32_t base = i < in_rows32 && k < K3 ? i * row_bytes + (uint32_t)g * 16u : kOutOfRange;
 #pragma unroll
             for (int kc = 0; kc < KS; ++kc)
@@ -322,7 +339,7 @@ __global__ __launch_bounds__((64 * UnionTile<K3, KCH, NB, CLS>::NW), (UnionTile<
         }
 #pragma unroll
         for (int b = 0; b < RB; ++b) {
-            const int rr = (wave * RB + b) * 16 + r16;
+            const int rr = wave * wave_rows + b * block_rows + r16;
             if (rr >= nrows) continue;
             const int64_t at = (row0 + rr) * Cout + c0 + v * 4 * EC;
             uint32_t u[EC / 2], w[EC / 2];
@@ -401,7 +418,10 @@ static void launch_union_tile(hipStream_t s, const ConvPlan& p, const void* in, 
     using T = UnionTile<K3, KCH, NB, CLS>;
     if constexpr (T::valid) {
         // a multiple of 8 workgroups: the kernel spreads the live tiles over the 8 XCDs
-        const unsigned grid = (unsigned)(((p.m_cap + T::R - 1) / T::R + 7) / 8 * 8 * (NB / T::NBT));
+        int64_t tiles = (p.m_cap + T::R - 1) / T::R;
+        if (T::SPREAD && p.m_out_dev)  // few live rows are spread over up to SLOTS tiles
+            tiles = std::max(tiles, std::min<int64_t>(T::SLOTS, (p.m_cap + 15) / 16));
+        const unsigned grid = (unsigned)((tiles + 7) / 8 * 8 * (NB / T::NBT));
         k_conv_union<DT, K3, KCH, NB, CLS><<<grid, 64 * T::NW, 0, s>>>(p.nbr, p.m_out_dev, p.m_cap, (const uint16_t*)in,
                                                                   in_rows, (const uint4*)wpack, scale, shift, relu,
                                                                   (const uint16_t*)p.res, (uint16_t*)out);

@@ -92,6 +92,27 @@ def test_conv_nbr_every_tile(spv, cin, cout, dtype):
         assert torch.equal(part.view(torch.int16), whole[:rows].view(torch.int16)), rows
 
 
+# A device row count far below the capacity that the tile was picked for: the live rows are spread over the chip
+# up to 49,152 of them (12 waves of 16 rows; 32,768 of 8 waves, half of that in two slices of 256 channels)
+@pytest.mark.parametrize("cin,cout,dtype", [(32, 32, "f16"), (96, 64, "bf16"), (128, 128, "bf16"), (256, 96, "f16"),
+                                            (64, 256, "f16"), (256, 256, "bf16")])
+def test_conv_nbr_few_live_rows(spv, cin, cout, dtype):
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(cin * 1000 + cout)
+    cap = 120_000
+    x, W = rand(gen, cap, cin, dtype=dt), rand(gen, 27, cin, cout, dtype=dt, std=(27 * cin) ** -0.5)
+    nbr = torch.randint(1, cap + 1, (cap, 27), generator=gen, device="cuda", dtype=torch.int32)
+    nbr[torch.rand(cap, 27, generator=gen, device="cuda") < 0.7] = 0
+    ws, P, res = spv.Workspace.for_ops(cap, 256), spv.spv_pack_weights(W), rand(gen, cap, cout, dtype=dt)
+    whole = spv.spv_sparse_conv_nbr_packed(ws, x, nbr, P, cout, cap, res=res)
+    for live in (0, 1, 17, 4096, 4097, 12_289, 16_384, 16_385, 32_769, 49_152, 49_153, 120_000):
+        out = torch.full((cap, cout), 7.0, dtype=dt, device="cuda")
+        spv.spv_sparse_conv_nbr_packed(ws, x, nbr, P, cout, cap, res=res, out=out,
+                                       m_out_dev=torch.tensor([live], dtype=torch.int64, device="cuda"))
+        assert torch.equal(out[:live].view(torch.int16), whole[:live].view(torch.int16)), live
+        assert bool((out[live:] == 7.0).all()), live
+
+
 # 16, 32 and 64 rows of a workgroup and the capacities at which the rule changes between them; widths
 # that are no multiple of 4 (element loads), of 16, and over one workgroup's 64 output channels
 @pytest.mark.parametrize("cin,cout,dtype", [(16, 16, "f32"), (5, 19, "f32"), (48, 70, "f32"), (6, 9, "bf16"),
