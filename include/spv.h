@@ -171,7 +171,9 @@ spv_status spv_kernel_map(void* stream, void* ws, size_t ws_bytes,
  * Out: out [m_out_cap][Cout] (dt); rows < *m_out_dev are written (m_out_dev
  *      NULL = m_out_cap).
  * bf16/f16 with Cin % 8 == 0 and Cout % 16 == 0 run on MFMA; other shapes and
- * f32 run on a float32 matrix-core kernel.
+ * f32 run on a float32 matrix-core kernel.  A 2x2x2 map by output (transposed = 0)
+ * runs on a table of its 8 offsets where the workspace has room for m_out_cap * 8
+ * int32 beside the rest, else on its pairs: the same results, more slowly.
  */
 spv_status spv_sparse_conv(void* stream, void* ws, size_t ws_bytes,
                            const void* in, int64_t in_rows, int32_t Cin,
@@ -634,9 +636,10 @@ spv_status spv_voxel_lookup(void* stream, const void* ws, size_t ws_bytes, int64
 /*
  * spv_conv_kernel -- the kernel spv_sparse_conv (and its sliced / dgrad forms)
  * runs on for a shape and its sizes, as the call decides it on the host:
- * 0 = the neighbour-table MFMA kernel (3x3x3 maps), 1 = the MFMA kernels of
+ * 0 = the neighbour-table MFMA kernel on a 3x3x3 map, 1 = the MFMA kernels of
  * the other maps and widths (2x2x2 maps by output at the neighbour-table
- * widths run on a table of 8, the rest on tiles of pairs),
+ * widths run on a table of 8, sparse transposed maps and the rest on tiles of
+ * pairs),
  * 2 = the float32 rows kernel; -1 for arguments the calls reject.  The
  * neighbour-table kernel addresses the input rows and its table with 32-bit
  * offsets: in_rows * Cin * 2 and m_out_cap * 27 * 4 must stay below

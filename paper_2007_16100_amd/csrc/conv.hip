@@ -16,7 +16,7 @@
 //   C_out in {32, 64, 96, 128, 256}; submanifold and strided 3x3x3 maps,
 //   and 2x2x2 stride-2 maps by output on a table of 8.
 //
-// * k_conv_tile (transposed maps -- where a 16-row union would be
+// * k_conv_tile (transposed stride-2 maps -- where a 16-row union would be
 //   mostly empty -- and the other widths): output rows in tiles of T with an
 //   LDS fp32 accumulator; the pairs of each (tile, offset) are a contiguous
 //   slice of the kernel map, multiplied 16 at a time and added into their

@@ -28,10 +28,10 @@ __device__ __forceinline__ void static_for(F&& f) {
 // of 16 bytes each, 64 bytes of a row side by side.  An odd NBT keeps the order of the packing (channels
 // nb*16 + 4g .. 4g+3, 8 bytes).
 //
-// What bounds it: at one 88k-voxel sweep 96 -> 96 the parts of a workgroup's life (weight copies, row
-// gathers, fragment reads, products) take 3 / 9 / 11 / 9 of its 48 us and mostly add up, and below
-// ~50k rows a workgroup's own chain of 27 offsets is the kernel's time, however few workgroups there
-// are.  So:
+// What bounds it: the waits in a workgroup's chain of 27 offsets.  On one 88k-voxel sweep, 96 -> 96 (47 us), the
+// matrix cores are busy 25% of the time and LDS 16%, 63% of the CUs' cycles have a wave, and a wave waits 43%
+// of its life (2% for LDS); below ~50k rows the chain of one workgroup is the kernel's time, however few
+// workgroups there are.  So:
 // * the workgroup's rows of the neighbour table go to LDS first, in one coalesced copy: read offset by
 //   offset from memory each 4-byte index cost a lane its own cache line, as much as a gathered row;
 // * the weights of a group of PH offsets are copied global->LDS while the group before is multiplied
@@ -388,7 +388,7 @@ bool union_supported(int K3, int Cin, int Cout, int dt) {
 // Which tile: whole rounds of workgroups over the 256 CUs times what one round takes.  A round of
 // workgroups of B blocks of 16 rows and FR weight fragments per offset measured about
 // 4 + 0.4 FR + B (0.1 + 0.28 KCH + 0.018 FR) us on 27 offsets (96 -> 96: 21 us at 8 blocks, 31 at 16, 43 at 24;
-// 32 -> 32: 8 at 8, 15 at 32; 256 -> 256 in slices of 128 channels: 88 at 16, of 64: 60 at 16, 30 at 8) and
+// 32 -> 32: 8 at 8, 15 at 32; 256 -> 256 in slices of 128 channels: 87 at 16, 61 at 8, of 64: 39 at 8) and
 // 1.5 + 0.13 FR + B (0.08 + 0.04 KCH + 0.016 FR) us on 8, beside the plan; so a small tile wins while it still
 // fits one round and a large one when rounds are many.  The model only ranks.  On 8 offsets, every tile of the
 // 25 width pairs timed at 19 sets of 354 to 188,994 coarse rows: the tile ranked first takes 1.1% longer than

@@ -702,7 +702,8 @@ def spv_voxel_lookup(ws: Workspace, n: int, qcoords: torch.Tensor) -> torch.Tens
 
 def spv_conv_kernel(K3: int, Cin: int, Cout: int, dtype: torch.dtype, in_rows: int, m_out_cap: int,
                     pair_cap: int, transposed: bool = False) -> int:
-    """Host query: 0 neighbour-table MFMA, 1 tile MFMA, 2 float32 rows, -1 rejected."""
+    """Host query: 0 neighbour-table MFMA on 27 offsets, 1 MFMA on a table of 8 or on tiles of pairs,
+    2 float32 rows, -1 rejected."""
     return lib().spv_conv_kernel(K3, Cin, Cout, _DT[dtype], in_rows, m_out_cap, pair_cap, int(transposed))
 
 

@@ -207,13 +207,13 @@ def test_conv_kernel_choice_at_the_32bit_offset_bound():
         assert spv.spv_block_conv_kernel(n_max, C, torch.bfloat16) == 0
         assert spv.spv_block_conv_kernel(n_max + 1, C, torch.bfloat16) == 2  # 27 n pairs exceed 32 bits too
         assert spv.spv_conv_kernel(27, C, C, torch.bfloat16, n_max, n_max, 27 * n_max) == 0
-        # too many input rows for either matrix-core kernel's 32-bit offsets: the vector-ALU kernel
+        # too many input rows for either 16-bit matrix-core kernel's 32-bit offsets: the rows kernel
         assert spv.spv_conv_kernel(27, C, C, torch.bfloat16, n_max + 1, 1000, 27 * 1000) == 2
     # the neighbour table itself: m_out * 27 * 4 bytes
     m_max = bound // (27 * 4)
     assert spv.spv_conv_kernel(27, 32, 32, torch.bfloat16, 1000, m_max, 0) == 0
     assert spv.spv_conv_kernel(27, 32, 32, torch.bfloat16, 1000, m_max + 1, 0) == 1
-    # fp32 and K = 2 never take the table kernel; a sparse transposed map takes the tile kernel
+    # fp32 and K = 2 never count as the table kernel of 27 offsets; a sparse transposed map takes the tile kernel
     assert spv.spv_conv_kernel(27, 32, 32, torch.float32, 1000, 1000, 27000) == 2
     assert spv.spv_conv_kernel(8, 64, 128, torch.bfloat16, 1000, 600, 1000) == 1
     assert spv.spv_conv_kernel(8, 128, 64, torch.bfloat16, 600, 1000, 1000, True) == 1

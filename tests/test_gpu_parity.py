@@ -518,8 +518,8 @@ def test_conv_k3_stride2_and_transposed_sweep(spv, sweep, cin, cout, dtype):
     (3, (128, 128), 64, 96, "f16", False),
     (3, (128, 128), 32, 32, "bf16", False),
     (3, (128, 128), 48, 80, "bf16", False),   # tile kernel (80 outputs)
-    (3, (40, 24), 16, 24, "f32", False),      # vector ALU
-    (2, (128, 128), 64, 96, "bf16", False),   # stride-2 tile kernel
+    (3, (40, 24), 16, 24, "f32", False),      # float32 rows kernel
+    (2, (128, 128), 64, 96, "bf16", False),   # table of 8
     (2, (128, 96), 96, 48, "bf16", True),     # transposed
 ])
 def test_conv_sliced_weights(spv, sweep, K, full, cin, cout, dtype, transposed):
@@ -745,7 +745,7 @@ def test_block_equals_stand_alone_ops(spv, sweep, mode, C):
 @pytest.mark.parametrize("C,dtype,nconv", [(16, "f32", 1), (16, "f32", 2), (48, "bf16", 2), (96, "bf16", 2)])
 def test_block_residual(spv, sweep, C, dtype, nconv):
     """Residual blocks (Sec. 3.3): the last conv adds the block's voxel input
-    before its ReLU -- through the vector-ALU (f32), tile (C = 48) and
+    before its ReLU -- through the float32 rows (f32), tile (C = 48) and
     neighbour-table (C = 96) conv kernels -- against the oracle's residual block."""
     xyz = sweep[::2] if C != 96 else sweep
     v = 0.05

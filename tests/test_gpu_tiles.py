@@ -1,5 +1,5 @@
-"""Kernels whose launch shape depends on the size of the call: every tile of the dispatch rules, at
-row counts just below, at and above the tile edges, against float64 on the same device."""
+"""Kernels whose launch shape depends on the size of the call, at row counts just below, at and above the
+tile edges and in every range of the dispatch rules, against float64 on the same device."""
 import pytest
 import torch
 
@@ -29,8 +29,8 @@ def close16(got, ref, dtype):
     assert bool((d <= ulp * ref.abs() + 2.0 ** -14 * ref.abs().max()).all()), float((d / ref.abs().max()).max())
 
 
-# rows around the tile edges (64, 128, 192, 256, 384 and 512 rows of a workgroup) and enough rows that
-# the rule takes each of its tiles; a table with and without 16-byte alignment; a device row count
+# rows around the tile edges (64, 128, 192, 256, 384 and 512 rows of a workgroup); a table with and without
+# 16-byte alignment; a device row count; the same bits again
 @pytest.mark.parametrize("cin,cout,dtype", [(32, 32, "bf16"), (96, 96, "f16"), (64, 128, "bf16"), (256, 96, "bf16"),
                                             (128, 256, "f16"), (256, 256, "bf16")])
 @pytest.mark.parametrize("m", [1, 65, 511, 9001, 31_100, 70_001, 110_003])
@@ -187,8 +187,8 @@ def stride2(spv, gen, m):
     return ws, km, mc, parent, kof
 
 
-# the 2x2x2 conv by output (tiles of 64 to 384 coarse rows) and the upsampling (64 or 128 coarse rows of a
-# workgroup, the output channels in one to eight passes), around the edges of their tiles
+# the 2x2x2 conv by output and the upsampling (64 or 128 coarse rows of a workgroup, the output channels in one
+# to eight passes), around the edges of their tiles
 @pytest.mark.parametrize("fine,coarse,dtype", [(32, 64, "bf16"), (96, 96, "f16"), (96, 128, "bf16"), (64, 256, "bf16"),
                                                (256, 32, "f16"), (256, 256, "bf16")])
 @pytest.mark.parametrize("m", [1, 130, 2049, 30_011, 90_001])
@@ -214,9 +214,8 @@ def test_stride2_tiles(spv, fine, coarse, dtype, m):
     has[parent[kof == 3]] = True
     assert bool((torch.isfinite(yi[:, 1].float()) == ~has).all())
     close16(yi[~has], (ref * sc + sh)[~has], dt)
-    # a workspace without room for the table of 8: the pairs themselves, as before
-    small = spv.Workspace(ws.nbytes)
-    small.nbytes = 4096 + 8 * (mc // 16 + 2) * 4 + 8 * max(fine, 32) * coarse * 2 + 1024
+    # a workspace without room for the table of 8: the pairs themselves
+    small = pairs_workspace(mc, fine, coarse)
     close16(spv.spv_sparse_conv(small, x, km.off, km.pairs, W, mc, scale=sc, shift=sh), ref * sc + sh, dt)
 
     z, Wt = rand(gen, mc, coarse, dtype=dt), rand(gen, 8, coarse, fine, dtype=dt, std=coarse ** -0.5)
