@@ -36,8 +36,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 //   offset from memory each 4-byte index cost a lane its own cache line, as much as a gathered row;
 // * the weights of a group of PH offsets are copied global->LDS while the group before is multiplied
 //   (two buffers, one barrier per group, instead of a stop for the copy at each group); where each of two
-//   buffers would hold one offset (48 fragments an offset and more), one buffer of two or three is filled
-//   between two barriers instead: 256 -> 96 on 29,789 rows 48 us, 55 with a barrier at every offset;
+//   buffers would hold one offset (48 fragments an offset and more, 32 in 384-row tiles), one buffer of two
+//   or three is filled between two barriers instead: 256 -> 96 on 29,789 rows 48 us, 55 with a barrier at
+//   every offset;
 // * the tile is chosen per call (launch_union_c below): 256 to 512 rows where the rows fill the chip, down to
 //   64 rows and a slice of the output channels where they do not, and 192 rows in between at 24 to 32 fragments
 //   an offset (128 -> 128 on 35,193 rows: 44 us, 49 in 256-row tiles).  256 -> 256 on 3,161 rows:

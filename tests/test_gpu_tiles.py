@@ -275,6 +275,12 @@ def test_down_every_tile(spv, cin, cout, dtype):
     for rows in (3000, 6001, 9003, 12_005, 23_000, 29_009, 40_003, 58_111, 70_001, mc):
         part = spv.spv_sparse_conv(ws, x, km.off, km.pairs, W, rows)
         assert torch.equal(part.view(torch.int16), pairs[:rows].view(torch.int16)), rows
+    for live in (0, 1, 5003, 33_001):  # of a buffer for all
+        out = torch.full((mc, cout), 7.0, dtype=dt, device="cuda")
+        spv.spv_sparse_conv(ws, x, km.off, km.pairs, W, mc, out=out,
+                            m_out_dev=torch.tensor([live], dtype=torch.int64, device="cuda"))
+        assert torch.equal(out[:live].view(torch.int16), pairs[:live].view(torch.int16)), live
+        assert bool((out[live:] == 7.0).all()), live
 
 
 # a 2x2x2 map read backwards has one offset per output row, also where the coarse side's buffer has the fine
